@@ -92,6 +92,16 @@ size_t ism_attn_workspace_size(int32_t op, int32_t batch, int32_t total_tokens,
                                int32_t max_seqlen, int32_t hq, int32_t hkv,
                                int32_t d, int32_t num_splits);
 
+/* Bytes of the optional workspace of a cached prefill (dense, paged or with
+ * 2-D positions; cache_cap = max_pages * page_size for a paged cache). A
+ * prefill that is given at least this much (256-byte aligned) may split its
+ * dialogues' key ranges over workgroups; without a workspace it runs
+ * unsplit, with the same result to rounding. 0: a workspace is not used. */
+size_t ism_attn_prefill_workspace_size(int32_t batch, int32_t total_new,
+                                       int32_t max_new, int32_t hq,
+                                       int32_t hkv, int32_t d,
+                                       int32_t cache_cap);
+
 /* Training / prefill forward over packed dialogues (Eq. 4 with the bound of
  * Eq. 5, softmax form). Writes o [T, hq, d] bf16 and lse [hq, T] fp32
  * (lse may be NULL). Workspace: ISM_OP_FWD. */
@@ -142,7 +152,8 @@ ism_status ism_attn_bwd(const ism_segments *sg, const void *q, const void *k,
  * (the lengths live on the device, so the call cannot check them): a
  * dialogue outside that range gets NaN in all its rows of o and lse, and
  * only its positions inside the cache are appended. max_new must be >= every
- * L_b. Workspace: ISM_OP_PREFILL_CACHED (none). */
+ * L_b. Workspace: none required (ism_attn_prefill_workspace_size gives the
+ * optional one). */
 ism_status ism_attn_prefill_cached(
     const int32_t *cu_seqlens_new, int32_t batch, int32_t total_new,
     int32_t max_new, const void *q_new, const void *k_new, const void *v_new,
@@ -182,10 +193,12 @@ ism_status ism_attn_prefill_cached_segment(
  * host, where the positions (device memory) are not. Workspace:
  * ism_attn_workspace_size(ISM_OP_DECODE, batch, 0, max_seqlen (with 0
  * replaced by cache_cap), hq, hkv, d, num_splits). Any hq / hkv is
- * supported: with 4 or more query heads per KV head a workgroup serves a
- * set of 4-32 of them on the matrix cores, otherwise 1-3 on the vector
- * ALU, except that a step with fewer than 512 (dialogue, KV head) pairs
- * runs every head set on the matrix cores. */
+ * supported: with 4 or more query heads per KV head, or on a step of fewer
+ * than 512 (dialogue, KV head) pairs, the step runs on the matrix cores,
+ * otherwise on the vector ALU. That size leaves room for about 640 chunks
+ * of all dialogues together; a smaller workspace, down to batch * hq *
+ * splits * (d + 2) * 4 bytes (rounded up) with one chunk per 256 keys, at
+ * most 64, or num_splits, is accepted and cuts fewer. */
 ism_status ism_attn_decode(const void *q, const void *k_new, const void *v_new,
                            void *k_cache, void *v_cache, int32_t cache_cap,
                            const int32_t *cache_seqlens, int32_t batch,
@@ -205,7 +218,8 @@ ism_status ism_attn_decode(const void *q, const void *k_new, const void *v_new,
  * before any launch. Every call on a device shares that device's scratch:
  * calls that may overlap on one device (different streams, no ordering
  * between them) race and must be serialised by the caller. Results equal
- * those of ism_attn_decode bit for bit. */
+ * those of ism_attn_decode given a workspace of the same size bit for bit
+ * (and given a larger one, unless that cuts more chunks). */
 #define ISM_NOALLOC_SCRATCH_BYTES (8u << 20)
 ism_status ism_attn_decode_noalloc(const void *q, const void *k_new,
                                    const void *v_new, void *k_cache,
@@ -227,8 +241,8 @@ ism_status ism_attn_decode_noalloc(const void *q, const void *k_new,
  * (this is cache_cap). The caller owns the pages and the table and
  * allocates the pages a turn appends to before the call; table entries are
  * read on the device and clamped into [0, num_pages). Results equal those
- * of the dense entry points on the same logical cache. Workspaces as for
- * ISM_OP_PREFILL_CACHED and ISM_OP_DECODE with cache_cap = max_pages *
+ * of the dense entry points on the same logical cache (and workspaces).
+ * Workspaces as for the dense entry points with cache_cap = max_pages *
  * page_size. */
 ism_status ism_attn_prefill_paged(
     const int32_t *cu_seqlens_new, int32_t batch, int32_t total_new,

@@ -33,7 +33,8 @@ HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall"]
 # per-source extras: the backward keeps MFMA accumulators in VGPRs (the
 # default AGPR form made the dK/dV kernel shuttle values between register
 # files on every tile)
-EXTRA_FLAGS = {"ism_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA_FLAGS = {"ism_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "ism_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def hipcc():

@@ -148,15 +148,10 @@ ism_status validate_new_lengths(const int32_t *cu_new, int32_t batch, int32_t to
   return ISM_OK;
 }
 
-// Split count of a decode step; `sets` = head sets per dialogue
-// (hq / decode_heads_per_set), `target` = workgroups to aim at: about 2048
-// four-wave workgroups (two rounds of four per CU) for the vector kernel;
-// for the matrix-core kernel, whose long chunks stream faster, about 512
-// one-wave workgroups on a dense cache and 768 on a paged one (on 256 slabs
-// of 8192 keys: 6.5 and 6.4 TB/s, against 6.2 and 6.4 with 768 for both,
-// 6.5 and 6.0 with 512, and 5.5 and 5.5 with 4096). At least 256 keys per
-// chunk, at most 64 chunks.
-constexpr int kSplitsVector = 2048, kSplitsMmaDense = 512, kSplitsMmaPaged = 768;
+// Split count of a vector-kernel decode step (1-3 query heads per KV head on
+// many slabs); `sets` = head sets per dialogue: about 2048 four-wave
+// workgroups (two rounds of four per CU), at least 256 keys per chunk, at
+// most 64 chunks.
 int decode_splits(int32_t batch, int32_t sets, int32_t max_len, int32_t req, int target) {
   if (req > 0) return req;
   const int slabs = batch * sets;
@@ -165,6 +160,88 @@ int decode_splits(int32_t batch, int32_t sets, int32_t max_len, int32_t req, int
   if (s > by_len) s = by_len;
   if (s > 64) s = 64;
   return s < 1 ? 1 : s;
+}
+
+// The smallest workspace a decode step accepts.
+constexpr int kSplitsVector = 2048, kSplitsMin = 768;
+size_t decode_min_workspace(int32_t batch, int32_t max_len, int32_t hq, int32_t hkv, int32_t d,
+                            int32_t req) {
+  const int sets = hq / ism::decode_heads_per_set(batch, hq, hkv);
+  const size_t s = (size_t)decode_splits(
+      batch, sets, max_len, req, ism::decode_vector(batch, hq, hkv) ? kSplitsVector : kSplitsMin);
+  return align_up((size_t)batch * hq * s * d * 4) + align_up((size_t)batch * hq * s * 2 * 4);
+}
+
+// The host part of a split-key launch (ism_split.hip): columns per workgroup
+// and how many units to make.
+struct SplitPlan {
+  int32_t colw, col_groups, col_stride, budget, max_units, max_splits;
+  // workspace of the partials and the plan (0: one chunk per dialogue)
+  size_t part_bytes, ml_bytes, plan_bytes;
+  size_t bytes() const { return part_bytes + ml_bytes + plan_bytes; }
+};
+
+constexpr int kSplitMinTiles = 4, kSplitUnits = 640, kSplitUnits64 = 960;  // measured in ism_split.hip
+SplitPlan split_plan(int32_t batch, int64_t total_rows, int32_t max_rows, int32_t hq, int32_t hkv, int32_t d,
+                     int64_t max_len, int32_t fixed, bool limited, size_t ws_bytes) {
+  SplitPlan p{};
+  const int64_t cols = (int64_t)max_rows * (hq / hkv);
+  p.colw = 32;
+  p.col_groups = (int32_t)((cols + 31) / 32);
+  p.col_stride = (int32_t)(cols < p.colw ? cols : p.colw);
+  p.budget = ((d == 64 ? kSplitUnits64 : kSplitUnits) + hkv - 1) / hkv;
+  const int64_t tiles = (max_len + ism::kSplitTile - 1) / ism::kSplitTile;
+  const int64_t most =
+      fixed > 0 ? fixed : (tiles + kSplitMinTiles - 1) / kSplitMinTiles;
+  p.max_splits = (int32_t)(most < 1 ? 1 : fixed <= 0 && most > 64 ? 64 : most);
+  // column groups of all dialogues together, partials of one unit over all
+  // KV heads
+  const int64_t by_rows = total_rows * (hq / hkv) / p.colw + batch, groups = p.col_groups;
+  const int64_t all_groups = by_rows < (int64_t)batch * groups ? by_rows : (int64_t)batch * groups;
+  const int64_t per = (int64_t)hkv * p.col_stride * (d + 2) * 4;
+  int64_t units = all_groups * p.max_splits;
+  if (fixed <= 0 && units > (int64_t)p.budget + all_groups) units = (int64_t)p.budget + all_groups;
+  const int64_t rest = (int64_t)align_up((size_t)batch * 2 * 4) + 2 * (int64_t)kAlign;
+  if (limited && p.max_splits > 1 && units * per + rest > (int64_t)ws_bytes) {
+    // a smaller workspace: fewer units, down to one chunk per dialogue
+    const int64_t fit = ((int64_t)ws_bytes - rest) / per;
+    if (fixed > 0 && fit >= all_groups) {
+      p.max_splits = (int32_t)(fit / all_groups);
+      units = all_groups * p.max_splits;
+    } else if (fixed <= 0 && fit > all_groups) {
+      p.budget = (int32_t)(fit - all_groups);
+      units = fit;
+    } else {
+      p.max_splits = 1;
+    }
+  }
+  if (p.max_splits == 1) {
+    p.max_units = (int32_t)all_groups;
+    return p;
+  }
+  p.max_units = (int32_t)units;
+  p.part_bytes = align_up((size_t)units * hkv * p.col_stride * d * 4);
+  p.ml_bytes = align_up((size_t)units * hkv * p.col_stride * 2 * 4);
+  p.plan_bytes = align_up((size_t)batch * 2 * 4);
+  return p;
+}
+
+void apply_plan(ism::SplitArgs &a, const SplitPlan &p, int32_t fixed, void *ws) {
+  a.colw = p.colw; a.col_groups = p.col_groups; a.col_stride = p.col_stride;
+  a.budget = p.budget; a.inv_budget = 1.0001f / (float)p.budget;
+  a.max_units = p.max_units; a.max_splits = p.max_splits;
+  a.min_tiles = kSplitMinTiles; a.fixed_splits = fixed;
+  a.part_o = (float *)ws;
+  a.part_ml = (float *)((char *)ws + p.part_bytes);
+  a.plan = p.max_splits > 1 ? (int32_t *)((char *)ws + p.part_bytes + p.ml_bytes) : nullptr;
+}
+
+// Cached prefills that run split: the (row, query head) pairs of the longest
+// new segment that share a KV head fill at most one 32-column block, so that
+// the cache is streamed once. (Two blocks would stream it twice: the
+// row-tiled forward kernel shares its K/V tiles among eight waves.)
+bool split_prefill(int32_t max_new, int32_t hq, int32_t hkv) {
+  return (int64_t)max_new * (hq / hkv) <= 32;
 }
 
 }  // namespace
@@ -184,16 +261,25 @@ extern "C" size_t ism_attn_workspace_size(int32_t op, int32_t batch,
       return 0;
     case ISM_OP_DECODE: {
       if (hkv < 1 || hq < hkv || hq % hkv) return 0;
-      // the larger of the dense and paged split counts
-      const int sets = hq / ism::decode_heads_per_set(batch, hq, hkv);
-      const size_t s = (size_t)decode_splits(
-          batch, sets, max_seqlen, num_splits,
-          ism::decode_mma_heads(batch, hq, hkv) > 0 ? kSplitsMmaPaged : kSplitsVector);
-      return align_up((size_t)batch * hq * s * d * 4) +
-             align_up((size_t)batch * hq * s * 2 * 4);
+      if (!ism::decode_vector(batch, hq, hkv)) {
+        const SplitPlan p = split_plan(batch, batch, 1, hq, hkv, d, max_seqlen, num_splits, false, 0);
+        const size_t need = decode_min_workspace(batch, max_seqlen, hq, hkv, d, num_splits);
+        return need > p.bytes() ? need : p.bytes();
+      }
+      return decode_min_workspace(batch, max_seqlen, hq, hkv, d, num_splits);
     }
   }
   return 0;
+}
+
+extern "C" size_t ism_attn_prefill_workspace_size(int32_t batch, int32_t total_new,
+                                                  int32_t max_new, int32_t hq, int32_t hkv,
+                                                  int32_t d, int32_t cache_cap) {
+  if (batch < 1 || total_new < 1 || max_new < 1 || hkv < 1 || hq < hkv || hq % hkv || d < 1 || cache_cap < 1 ||
+      !split_prefill(max_new, hq, hkv))
+    return 0;
+  const SplitPlan p = split_plan(batch, total_new, max_new, hq, hkv, d, cache_cap, 0, false, 0);
+  return p.bytes();
 }
 
 extern "C" ism_status ism_attn_fwd(const ism_segments *sg, const void *q,
@@ -362,7 +448,12 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
     if (!rp->pos1 || !rp->pos2) return fail(ISM_ERR_NULL, "pos1_new and pos2_new are required");
     if ((st = check_rope_base(rp->base))) return st;
   }
-  (void)ws; (void)ws_bytes;
+  const size_t split_need =
+      ism_attn_prefill_workspace_size(batch, total_new, max_new, hq, hkv, d, cache_cap);
+  // (no need: short caches, one chunk per dialogue)
+  const bool split =
+      split_prefill(max_new, hq, hkv) &&
+      (split_need == 0 || (ws && (uintptr_t)ws % kAlign == 0 && ws_bytes >= split_need));
   if ((st = check_device())) return st;
   if ((st = validate_new_lengths(cu_seqlens_new, batch, total_new, max_new,
                                  (hipStream_t)stream)))
@@ -370,17 +461,44 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
 
   hipStream_t s = (hipStream_t)stream;
   const float l2b = rp ? log2f(rp->base) : 0.f;
-  const hipError_t ae =
-      rp ? ism::launch_cache_append_rope(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
-                                         cache_seqlens, rp->pos1, rp->pos2, l2b, batch, max_new,
-                                         hkv, d, cache_cap, s)
-      : pg ? ism::launch_cache_append_paged(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
-                                          cache_seqlens, pg->block_table, pg->max_pages,
-                                          pg->num_pages, pg->page_size, batch, max_new, hkv, d,
-                                          s)
-         : ism::launch_cache_append(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
-                                    cache_seqlens, batch, max_new, hkv, d, cache_cap, s);
+  hipError_t ae = hipSuccess;
+  if (rp)
+    ae = ism::launch_cache_append_rope(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
+                                       cache_seqlens, rp->pos1, rp->pos2, l2b, batch, max_new,
+                                       hkv, d, cache_cap, s);
+  else if (split)
+    ;  // the split kernel appends
+  else if (pg)
+    ae = ism::launch_cache_append_paged(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
+                                        cache_seqlens, pg->block_table, pg->max_pages,
+                                        pg->num_pages, pg->page_size, batch, max_new, hkv, d, s);
+  else
+    ae = ism::launch_cache_append(k_new, v_new, k_cache, v_cache, cu_seqlens_new, cache_seqlens,
+                                  batch, max_new, hkv, d, cache_cap, s);
   if ((st = hip_status(ae, "cache append launch"))) return st;
+  if (split) {
+    ism::SplitArgs a{};
+    a.q = q_new; a.k_new = k_new; a.v_new = v_new; a.k_cache = k_cache; a.v_cache = v_cache;
+    a.cu_new = cu_seqlens_new; a.cache_len = cache_seqlens; a.o = o; a.lse = lse;
+    a.batch = batch; a.hq = hq; a.hkv = hkv; a.group = hq / hkv; a.cap = cache_cap;
+    a.total_q = total_new; a.max_rows = max_new;
+    a.scale = scale;
+    a.causal = seg_is_query ? 0 : 1;
+    a.append = rp ? 0 : 1;
+    apply_plan(a, split_plan(batch, total_new, max_new, hq, hkv, d, cache_cap, 0, false, 0), 0, ws);
+    if (pg) {
+      a.block_table = pg->block_table;
+      a.max_pages = pg->max_pages;
+      a.num_pages = pg->num_pages;
+      a.page_size = pg->page_size;
+    }
+    if (rp) {
+      a.rope_pos1 = rp->pos1;
+      a.rope_pos2 = rp->pos2;
+      a.rope_log2_base = l2b;
+    }
+    return hip_status(ism::launch_split(a, d, s), "cached prefill launch");
+  }
   ism::FwdArgs a{};
   a.q = q_new; a.k = k_cache; a.v = v_cache; a.o = o; a.lse = lse;
   a.cu_q = cu_seqlens_new;
@@ -504,14 +622,30 @@ ism_status decode_impl(const void *q, const void *k_new, const void *v_new, void
                 cache_cap);
   if (num_splits < 0 || num_splits > 1024)
     return fail(ISM_ERR_SHAPE, "num_splits %d outside [0, 1024]", num_splits);
-  const int set_heads = ism::decode_heads_per_set(batch, hq, hkv);
-  const bool mma = ism::decode_mma_heads(batch, hq, hkv) > 0;
-  const int splits = decode_splits(batch, hq / set_heads, max_seqlen, num_splits,
-                                   !mma ? kSplitsVector : pg ? kSplitsMmaPaged : kSplitsMmaDense);
-  const size_t need = ism_attn_workspace_size(ISM_OP_DECODE, batch, 0, max_seqlen, hq,
-                                              hkv, d, num_splits);
+  const bool vec = ism::decode_vector(batch, hq, hkv);
+  const size_t need = decode_min_workspace(batch, max_seqlen, hq, hkv, d, num_splits);
   if ((st = check_ws(ws, ws_bytes, need))) return st;
   if ((st = check_device())) return st;
+  if (!vec) {
+    ism::SplitArgs a{};
+    a.q = q; a.k_new = k_new; a.v_new = v_new; a.k_cache = k_cache; a.v_cache = v_cache;
+    a.cache_len = cache_seqlens; a.o = o; a.lse = lse;
+    a.batch = batch; a.hq = hq; a.hkv = hkv; a.group = hq / hkv; a.cap = cache_cap;
+    a.total_q = batch; a.max_rows = 1;
+    a.scale = scale;
+    a.append = 1;
+    apply_plan(a, split_plan(batch, batch, 1, hq, hkv, d, max_seqlen, num_splits, true, ws_bytes),
+               num_splits, ws);
+    if (pg) {
+      a.block_table = pg->block_table;
+      a.max_pages = pg->max_pages;
+      a.num_pages = pg->num_pages;
+      a.page_size = pg->page_size;
+    }
+    return hip_status(ism::launch_split(a, d, (hipStream_t)stream), "decode launch");
+  }
+  const int set_heads = ism::decode_heads_per_set(batch, hq, hkv);
+  const int splits = decode_splits(batch, hq / set_heads, max_seqlen, num_splits, kSplitsVector);
 
   ism::DecodeArgs a{};
   a.q = q; a.k_new = k_new; a.v_new = v_new;
@@ -523,7 +657,6 @@ ism_status decode_impl(const void *q, const void *k_new, const void *v_new, void
   a.splits = splits;
   a.scale = scale;
   a.set_heads = set_heads;
-  a.mma = mma ? 1 : 0;
   if (pg) {
     a.block_table = pg->block_table;
     a.max_pages = pg->max_pages;
@@ -613,8 +746,7 @@ extern "C" ism_status ism_attn_decode_noalloc(const void *q, const void *k_new,
     return fail(ISM_ERR_CAPACITY, "max_seqlen %d outside [1, cache_cap=%d]", ms, cache_cap);
   if (num_splits < 0 || num_splits > 1024)
     return fail(ISM_ERR_SHAPE, "num_splits %d outside [0, 1024]", num_splits);
-  const size_t need = ism_attn_workspace_size(ISM_OP_DECODE, batch, 0, ms, hq, hkv, d,
-                                              num_splits);
+  const size_t need = decode_min_workspace(batch, ms, hq, hkv, d, num_splits);
   if (need > ISM_NOALLOC_SCRATCH_BYTES)
     return fail(ISM_ERR_WORKSPACE,
                 "split partials need %zu bytes, above the %zu-byte scratch of the "

@@ -267,6 +267,22 @@ __device__ __forceinline__ bf16x8 tr_operand_at(const char *lds, uint32_t off_lo
   return __builtin_bit_cast(bf16x8, v);
 }
 
+// The same two reads from LDS byte addresses: a row operand, and a transposed
+// operand OFF bytes past the two addresses.
+__device__ __forceinline__ bf16x8 lds_row_operand(uint32_t addr) {
+  typedef const __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+  return *(lds_bf16x8 *)addr;
+}
+template <int OFF>
+__device__ __forceinline__ bf16x8 lds_tr_operand(uint32_t lo, uint32_t hi) {
+  typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+  typedef __attribute__((address_space(3))) char lds_char;
+  const i16x4 v[2] = {
+      __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)((lds_char *)lo + OFF)),
+      __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4 *)((lds_char *)hi + OFF))};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
 // Per-lane byte offsets for reading MFMA A operands from a swizzled,
 // unpadded tile of D bf16 per row.
 //  * row operand (ds_read_b128): tile rows r0 + (lane % 32), r0 % 16 == 0,
@@ -428,6 +444,30 @@ __device__ __forceinline__ void rope_rotate8(u32x4 &a, u32x4 &b, const float (&c
     const float v1 = fmaf(x1, s[2 * i + 1], y1 * c[2 * i + 1]);
     a[i] = pack_bf16x2(u0, u1);
     b[i] = pack_bf16x2(v0, v1);
+  }
+}
+
+// 2-D rotary positions of one query row held as MFMA operands: qf[ks] holds
+// dims 16 ks + 8 hf .. + 7, so each pair (k, k + D/4) of a half lies in
+// qf[ks] and qf[ks + D/64] of the same lane.
+template <int D>
+__device__ __forceinline__ void rope_queries(bf16x8 (&qf)[D / 16], int hf, int p1, int p2,
+                                             float log2_base) {
+  constexpr int NKS = D / 16, QK = NKS / 4;  // k steps per quarter of the head
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+#pragma unroll
+    for (int j = 0; j < QK; ++j) {
+      const int ks = half * (NKS / 2) + j;
+      const int ci = 2 * j + hf;  // 8-dim chunk inside the half's first quarter
+      float c[8], s[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rope_cs(half ? p2 : p1, ci * 8 + e, D / 2, log2_base, c[e], s[e]);
+      u32x4 x = __builtin_bit_cast(u32x4, qf[ks]), y = __builtin_bit_cast(u32x4, qf[ks + QK]);
+      rope_rotate8(x, y, c, s);
+      qf[ks] = __builtin_bit_cast(bf16x8, x);
+      qf[ks + QK] = __builtin_bit_cast(bf16x8, y);
+    }
   }
 }
 

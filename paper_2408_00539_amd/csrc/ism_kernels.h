@@ -110,21 +110,22 @@ struct DecodeArgs {
   const int32_t *block_table;
   int32_t page_size, max_pages, num_pages;
   int32_t set_heads;  // query heads per workgroup (decode_heads_per_set)
-  int32_t mma;        // the matrix-core kernel (decode_mma_heads > 0)
 };
 
 hipError_t launch_decode(const DecodeArgs &a, int d, hipStream_t stream);
 
-// Decode head sets, with G = hq / hkv query heads per KV head: the
-// matrix-core kernel takes sets of the largest divisor of G up to 32 (the
-// columns of one product) when that is 4 or more, or, when the step has
-// fewer than kDecodeVectorSlabs (dialogue, KV head) slabs, of any size;
-// 0 otherwise. Below that slab count its long one-wave chunks stream faster
-// than the vector kernel even for one query head (256 slabs of 8192
-// positions: 6.5 TB/s against 6.2, 6.0 and 5.9 for 1, 2 and 3 heads; 64
-// slabs: 5.6 against 5.2, 4.8 and 4.2); from 1024 slabs on the vector
-// kernel's wider grid is faster for 1-3 heads (6.9, 6.7, 6.7 against 6.4).
+// Which kernel a decode step takes, with G = hq / hkv query heads per KV head:
+// the vector kernel (ism_decode.hip) when the step has kDecodeVectorSlabs or
+// more (dialogue, KV head) slabs and no divisor of G lies in 4 .. 32, else the
+// split-key matrix-core kernel (ism_split.hip). Below that slab count the
+// latter's long one-wave chunks stream faster even for one query head (256
+// slabs of 8192 positions: 6.5 TB/s against 6.2, 6.0 and 5.9 for 1, 2 and 3
+// heads; 64 slabs: 5.6 against 5.2, 4.8 and 4.2); from 1024 slabs on the
+// vector kernel's wider grid is faster for 1-3 heads (6.9, 6.7, 6.7 against
+// 6.4).
 constexpr int kDecodeVectorSlabs = 512;
+// The head set whose partials size the smallest workspace a step accepts (the
+// largest divisor of G up to 32; 0: a vector-kernel step).
 inline int decode_mma_heads(int batch, int hq, int hkv) {
   const int g = hq / hkv;
   const int lo = (int64_t)batch * hkv < kDecodeVectorSlabs ? 1 : 4;
@@ -132,14 +133,54 @@ inline int decode_mma_heads(int batch, int hq, int hkv) {
     if (g % s == 0) return s;
   return 0;
 }
-// Query heads per decode workgroup: the matrix-core set, else (vector kernel,
-// G without a divisor between 4 and 32) the largest divisor of G up to 3.
+inline bool decode_vector(int batch, int hq, int hkv) {
+  return decode_mma_heads(batch, hq, hkv) == 0;
+}
+// Query heads per set: that, or for the vector kernel (whose workgroups serve
+// one set) the largest divisor of G up to 3.
 inline int decode_heads_per_set(int batch, int hq, int hkv) {
   const int m = decode_mma_heads(batch, hq, hkv);
   if (m) return m;
   const int g = hq / hkv;
   return g % 3 == 0 ? 3 : g % 2 == 0 ? 2 : 1;
 }
+
+// Attention of the new rows of each dialogue over its cache with the keys
+// split over workgroups (ism_split.hip); the host part of its plan.
+constexpr int kSplitTile = 32;  // keys per tile
+struct SplitArgs {
+  const void *q;             // [total_q, hq, d]
+  const void *k_new, *v_new; // [total_q, hkv, d]
+  void *k_cache, *v_cache;   // [batch, hkv, cap, d] (or page pools)
+  const int32_t *cu_new;     // [batch + 1] row ranges; null: one row per dialogue
+  const int32_t *cache_len;  // [batch] cached tokens before the call
+  void *o;                   // [total_q, hq, d]
+  float *lse;                // [hq, total_q] or null
+  float *part_o;             // [max_units * hkv, col_stride, d]
+  float *part_ml;            // [max_units * hkv, col_stride, 2]
+  int32_t *plan;             // [batch, 2] chunks and first slot (null: always one chunk)
+  int32_t batch, hq, hkv, group, cap, total_q, max_rows;
+  float scale;
+  int32_t causal;            // row r sees keys [0, C_b + r], else all
+  int32_t append;            // read new rows from the input, store them into the cache
+  int32_t colw;              // columns (row, head) per workgroup: 32 per wave
+  int32_t col_groups;        // column groups of the longest dialogue
+  int32_t col_stride;        // columns per partials slot
+  int32_t budget;            // units (chunk, column group) per KV head to aim at
+  float inv_budget;          // 1 / budget, rounded up a little
+  int32_t max_units;         // bound of the units per KV head
+  int32_t max_splits;        // chunks per dialogue at most
+  int32_t min_tiles;         // tiles per chunk at least (automatic plan)
+  int32_t fixed_splits;      // > 0: that many chunks per dialogue
+  // paged cache (see FwdArgs)
+  const int32_t *block_table;
+  int32_t page_size, max_pages, num_pages;
+  // 2-D rotary positions of the new rows (see FwdArgs)
+  const int32_t *rope_pos1, *rope_pos2;
+  float rope_log2_base;
+};
+
+hipError_t launch_split(const SplitArgs &a, int d, hipStream_t stream);
 
 struct BwdArgs {
   const void *q, *k, *v, *o, *dout;

@@ -54,6 +54,7 @@ _Z = ctypes.c_size_t
 
 _SIGS = {
     "ism_attn_workspace_size": (_Z, [_I, _I, _I, _I, _I, _I, _I, _I]),
+    "ism_attn_prefill_workspace_size": (_Z, [_I, _I, _I, _I, _I, _I, _I]),
     "ism_attn_fwd": (_I, [ctypes.POINTER(ism_segments), _P, _P, _P, _P, _P,
                           _I, _I, _I, _F, _P, _Z, _P]),
     "ism_attn_bwd": (_I, [ctypes.POINTER(ism_segments), _P, _P, _P, _P, _P,
@@ -144,6 +145,11 @@ def workspace_size(op, batch=0, total_tokens=0, max_seqlen=0, hq=0, hkv=0,
     return int(lib().ism_attn_workspace_size(op, batch, total_tokens,
                                              max_seqlen, hq, hkv, d,
                                              num_splits))
+
+
+def prefill_workspace_size(batch, total_new, max_new, hq, hkv, d, cache_cap):
+    return int(lib().ism_attn_prefill_workspace_size(
+        batch, total_new, max_new, hq, hkv, d, cache_cap))
 
 
 def _outputs(out, specs, device):
@@ -312,18 +318,20 @@ def _prefill(seg_is_query, q_new, k_new, v_new, k_cache, v_cache,
     o, lse = _outputs(out, [("o", torch.bfloat16, (Tn, hq, d)),
                             ("lse", torch.float32,
                              (hq, Tn) if return_lse else None)], q_new.device)
+    nws = prefill_workspace_size(B, Tn, int(max_new), hq, hkv, d, cap)
+    ws = _workspace(nws, q_new.device)
     if seg_is_query is None:
         _check(lib().ism_attn_prefill_cached(
             _ptr(cu_seqlens_new), B, Tn, int(max_new), _ptr(q_new),
             _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), cap,
-            _ptr(cache_seqlens), _ptr(o), _ptr(lse), hq, hkv, d, scale, None,
-            0, _stream()))
+            _ptr(cache_seqlens), _ptr(o), _ptr(lse), hq, hkv, d, scale,
+            _ptr(ws), nws, _stream()))
     else:
         _check(lib().ism_attn_prefill_cached_segment(
             _ptr(cu_seqlens_new), B, Tn, int(max_new), int(seg_is_query),
             _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache),
             _ptr(v_cache), cap, _ptr(cache_seqlens), _ptr(o), _ptr(lse), hq,
-            hkv, d, scale, None, 0, _stream()))
+            hkv, d, scale, _ptr(ws), nws, _stream()))
     return o, lse
 
 
@@ -382,11 +390,13 @@ def prefill_cached_rope2d(q_new, k_new, v_new, k_cache, v_cache, cache_seqlens,
     o = torch.empty_like(q_new)
     lse = torch.empty((hq, Tn), dtype=torch.float32, device=q_new.device) \
         if return_lse else None
+    nws = prefill_workspace_size(B, Tn, int(max_new), hq, hkv, d, cap)
+    ws = _workspace(nws, q_new.device)
     _check(lib().ism_attn_prefill_cached_rope2d(
         _ptr(cu_seqlens_new), B, Tn, int(max_new), int(bool(seg_is_query)),
         _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), cap,
         _ptr(cache_seqlens), _ptr(pos1_new), _ptr(pos2_new), float(base), _ptr(o),
-        _ptr(lse), hq, hkv, d, scale, None, 0, _stream()))
+        _ptr(lse), hq, hkv, d, scale, _ptr(ws), nws, _stream()))
     return o, lse
 
 
@@ -506,11 +516,13 @@ def prefill_paged(q_new, k_new, v_new, k_pages, v_pages, block_table,
     o = torch.empty_like(q_new)
     lse = torch.empty((hq, Tn), dtype=torch.float32, device=q_new.device) \
         if return_lse else None
+    nws = prefill_workspace_size(B, Tn, int(max_new), hq, hkv, d, mp * ps)
+    ws = _workspace(nws, q_new.device)
     _check(lib().ism_attn_prefill_paged(
         _ptr(cu_seqlens_new), B, Tn, int(max_new), int(bool(seg_is_query)),
         _ptr(q_new), _ptr(k_new), _ptr(v_new), _ptr(k_pages), _ptr(v_pages),
         P, ps, _ptr(block_table), mp, _ptr(cache_seqlens), _ptr(o), _ptr(lse),
-        hq, hkv, d, scale, None, 0, _stream()))
+        hq, hkv, d, scale, _ptr(ws), nws, _stream()))
     return o, lse
 
 

@@ -1,0 +1,126 @@
+"""GPU parity of the split-key cache kernel (ism_split.hip) where its plan and
+its tiles can go wrong: column counts (new rows x query heads per KV head)
+around one 32-column block, histories at the edges of the 32-key tiles, more
+dialogues than lanes of the planning wave, dialogues without new rows, ragged
+lengths that are cut into one to many chunks, workspaces from none to full,
+and out-of-contract lengths. Against the fp64 oracle, with outputs filled
+with NaN; paged equal to dense bit for bit, and the caches after the append
+equal to the inputs.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2408_00539_amd import workloads as W
+from tests._gpu import announce, compare, dev_bf16, f64, host_f64, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+def _bits(rng, *shape):
+    return W.to_bf16_bits(rng.standard_normal(shape, dtype=np.float32))
+
+
+def _hist(rng, batch, longest):
+    edges = [min(x, longest) for x in (0, 1, 31, 32, 33, 63, 64, 127, 128, 129, longest)]
+    more = rng.integers(0, longest + 1, size=max(0, batch - len(edges)))
+    return np.concatenate([edges, more])[:batch].astype(np.int32)
+
+
+@pytest.mark.parametrize("batch,longest,hq,hkv,d,new,is_query", [
+    (11, 2100, 8, 2, 128, 8, False),    # 32 columns, many chunks
+    (11, 2100, 3, 1, 64, 10, False),    # 30 columns, group of 3
+    (11, 700, 8, 2, 128, 9, True),      # 36 columns: the row-tiled kernel
+    (5, 130, 1, 1, 64, 32, False),      # no grouping
+    (70, 300, 4, 1, 128, 4, False),     # more dialogues than lanes
+    (130, 90, 2, 2, 64, 3, True),
+])
+def test_ragged_chunks(batch, longest, hq, hkv, d, new, is_query):
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    rng = np.random.default_rng(batch * 7 + longest + hq + d + new)
+    hist = _hist(rng, batch, longest)
+    lens = rng.integers(0, new + 1, size=batch)  # some dialogues get no row
+    lens[:2] = new
+    cap, ps = -(-(longest + new) // 64) * 64, 64
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    kc, vc = _bits(rng, batch, hkv, cap, d), _bits(rng, batch, hkv, cap, d)
+    q, k, v = (_bits(rng, cu[-1], n, d) for n in (hq, hkv, hkv))
+    Kc, Vc = dev_bf16(kc), dev_bf16(vc)
+    mp = cap // ps
+    order = rng.permutation(batch * mp + 3)[:batch * mp].reshape(batch, mp).astype(np.int32)
+    Kp = torch.zeros((batch * mp + 3, hkv, ps, d), dtype=torch.bfloat16, device="cuda")
+    Vp = torch.zeros_like(Kp)
+    tab = torch.from_numpy(order).cuda()
+    for pool, cache in ((Kp, Kc), (Vp, Vc)):
+        pool[tab.long().reshape(-1)] = cache.view(batch, hkv, mp, ps, d).transpose(1, 2).reshape(
+            batch * mp, hkv, ps, d)
+    dev = dev_bf16(q), dev_bf16(k), dev_bf16(v)
+    tl, tc = torch.from_numpy(hist).cuda(), torch.from_numpy(cu).cuda()
+    o = torch.full((int(cu[-1]), hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((hq, int(cu[-1])), float("nan"), device="cuda")
+    announce("split chunks", batch, longest, hq, hkv, d, new, is_query)
+    ops.prefill_cached_segment(*dev, Kc, Vc, tl, tc, new, is_query, out=(o, lse))
+    op, lp = ops.prefill_paged(*dev, Kp, Vp, tab, tl, tc, new, is_query)
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), op.view(torch.int16)) and torch.equal(lse, lp)
+    ro, rl = np.empty((cu[-1], hq, d)), np.empty((hq, cu[-1]))
+    for b in range(batch):
+        r, C, L = slice(cu[b], cu[b + 1]), int(hist[b]), int(lens[b])
+        if not L:
+            continue
+        ro[r], rl[:, r], _, _ = oracle.prefill_cached(
+            f64(kc[b, :, :C]).transpose(1, 0, 2), f64(vc[b, :, :C]).transpose(1, 0, 2), f64(q[r]),
+            f64(k[r]), f64(v[r]), 1 / np.sqrt(d), new_is_query=is_query)
+        kc[b, :, C:C + L] = k[r].transpose(1, 0, 2)
+        vc[b, :, C:C + L] = v[r].transpose(1, 0, 2)
+    compare("O split", host_f64(o), ro)
+    compare("LSE split", host_f64(lse), rl)
+    for cache, pool, want in ((Kc, Kp, kc), (Vc, Vp, vc)):
+        np.testing.assert_array_equal(cache.view(torch.int16).cpu().numpy().view(np.uint16), want)
+        back = pool[tab.long().reshape(-1)].view(batch, mp, hkv, ps, d).transpose(1, 2).reshape(
+            batch, hkv, cap, d)
+        assert torch.equal(back.view(torch.int16), cache.view(torch.int16))
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (40, 1, 64)])  # 4 and 40 columns
+def test_decode_workspaces(hq, hkv, d):
+    """The same step with every workspace the call accepts, from the smallest
+    (fewer chunks, down to one per dialogue) to more than it uses; one
+    dialogue's position lies outside the cache (NaN, nothing appended)."""
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    rng = np.random.default_rng(hq + d)
+    B, cap = 9, 3000
+    pos = np.array([0, 1, 31, 32, 2999, 3000, 1500, 700, 64], np.int32)
+    kc, vc = _bits(rng, B, hkv, cap, d), _bits(rng, B, hkv, cap, d)
+    q, k, v = _bits(rng, B, hq, d), _bits(rng, B, hkv, d), _bits(rng, B, hkv, d)
+    want = [oracle.decode_step(f64(kc[b, :, :p]).transpose(1, 0, 2),
+                               f64(vc[b, :, :p]).transpose(1, 0, 2), f64(q[b]), f64(k[b]),
+                               f64(v[b]), 1 / np.sqrt(d))[:2] if p < cap else None
+            for b, p in enumerate(pos)]
+    full = ops.workspace_size(ops.ISM_OP_DECODE, B, 0, cap, hq, hkv, d)
+    least = full
+    for nbytes in (full + 4096, full, full // 2 // 256 * 256, full // 8 // 256 * 256, 256):
+        Kc, Vc = dev_bf16(kc), dev_bf16(vc)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        announce("decode workspace", hq, hkv, d, nbytes)
+        try:
+            o, lse = ops.decode(dev_bf16(q), dev_bf16(k), dev_bf16(v), Kc, Vc,
+                                torch.from_numpy(pos).cuda(), workspace=ws)
+        except ops.IsmError as e:
+            assert "ISM_ERR_WORKSPACE" in str(e) and nbytes < full
+            continue
+        least = min(least, nbytes)
+        o, lse = host_f64(o), host_f64(lse)
+        got = Kc.view(torch.int16).cpu().numpy().view(np.uint16)
+        for b, p in enumerate(pos):
+            if p >= cap:
+                assert np.isnan(o[b]).all() and np.isnan(lse[:, b]).all()
+                np.testing.assert_array_equal(got[b], kc[b])
+                continue
+            compare(f"O ws {nbytes} b{b}", o[b], want[b][0])
+            compare(f"LSE ws {nbytes} b{b}", lse[:, b], want[b][1])
+            np.testing.assert_array_equal(got[b, :, p], k[b])
+    assert least < full or hkv == 1
