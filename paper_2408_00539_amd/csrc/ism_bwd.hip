@@ -748,10 +748,12 @@ int gcd_i(int x, int y) {
   return x;
 }
 
-// dQ workgroups of NWV waves. Eight waves (one workgroup per CU) share each
-// staged K/V tile among twice the rows (or the heads of a KV group) of four
-// waves: half the transfers per product, measured 1.5-2 % faster on the
-// backward than two 4-wave workgroups per CU.
+// dQ workgroups of four waves, two to a CU, so that one's prologue and last
+// steps run beside the other's products. Eight waves (alone on a CU, half the
+// transfers per product) measured the same on 4 x 8192 tokens (2575 us
+// against 2542 with four) and slower on shorter dialogues (12 ragged ones up
+// to 3001 tokens, 32/8 heads: 945 against 873 us; 6 up to 900, d 64: 24.4
+// against 18.1).
 template <int D, int NWV>
 hipError_t launch_dq(const BwdArgs &a, hipStream_t stream) {
   const int hpw = gcd_i(a.hq / a.hkv, NWV);
@@ -766,7 +768,7 @@ hipError_t launch_dq(const BwdArgs &a, hipStream_t stream) {
 // dQ first: it also writes the per-row summands the dK/dV kernel reads.
 template <int D>
 hipError_t launch_bwd_t(const BwdArgs &a, hipStream_t stream) {
-  hipError_t err = launch_dq<D, 8>(a, stream);
+  hipError_t err = launch_dq<D, 4>(a, stream);
   if (err != hipSuccess) return err;
   const int ktiles = (a.max_seqlen + kKW - 1) / kKW;
   hipLaunchKernelGGL((dkv_kernel<D>), dim3((unsigned)xcd_grid((int64_t)a.batch * a.hkv, ktiles)),

@@ -46,15 +46,16 @@ hipError_t launch_prep_lim(const int32_t *cu_segs, const uint8_t *seg_is_query,
   return hipGetLastError();
 }
 
-// Occupancy target in waves per SIMD (1 or 2), which bounds registers.
-#ifndef ISM_FWD_WPE
-#define ISM_FWD_WPE 2
-#endif
-
 namespace {
 
 constexpr int kBN = 64;  // keys per tile
 constexpr int kQW = 32;  // query rows per wave
+
+// Waves per SIMD, which bounds registers: d = 64 fits a third wave (4 x 8000
+// tokens, 16 heads: 420 -> 398 us; not the paged cache, which would spill).
+constexpr int fwd_occupancy(int d, int waves, bool paged) {
+  return d == 64 && waves == 4 && !paged ? 3 : 2;
+}
 
 // K and V tiles of 64 keys, row-major, unpadded rows of D bf16 with the
 // swz<D>() chunk swizzle, double-buffered; filled by direct global->LDS
@@ -249,7 +250,7 @@ __device__ __forceinline__ float step_block(const char *kl, const char *vl,
 // cost the L2 sharing between them: the workload-3 prefill ran 22 % slower).
 template <int D, bool CACHE, int NWV, bool PAGED, bool NT>
 __global__ void __launch_bounds__(NWV * 64)
-__attribute__((amdgpu_waves_per_eu(ISM_FWD_WPE, ISM_FWD_WPE)))
+__attribute__((amdgpu_waves_per_eu(fwd_occupancy(D, NWV, PAGED), fwd_occupancy(D, NWV, PAGED))))
 fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
   constexpr int NDB = D / 32;      // 32-wide d blocks of the output
   constexpr int NKS = D / 16;      // 16-deep k steps of Q K^T
@@ -506,15 +507,28 @@ hipError_t launch_fwd_w(const FwdArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Grouped KV heads run 8-wave workgroups (one per CU): the heads of a group
-// and two 32-row blocks share each staged K/V tile, half the transfers per
-// product of 4-wave workgroups. Without grouping, 8 waves would be 256 rows
-// of one head, whose waves finish at different key tiles; 4 waves (two
-// workgroups per CU) measure as fast there.
+// Four-wave workgroups, two (three at d = 64) to a CU, so that one's prologue
+// and last steps run beside another's products. Eight-wave workgroups stage
+// each K/V tile for twice the columns, half the transfers per product, but
+// are alone on their CU: with grouped KV heads (the heads of a group share
+// every tile) they still win on long key loops, where the prologue is small,
+// and on cached prefills that fill the chip, whose K/V come from HBM.
+// Measured, 8 waves against 4 (us): packed 32/8 heads 2 x 16384 3733, 3752;
+// 6 ragged dialogues up to 3000 348, 330; 24/8 heads 12 x 900 74, 60; cached
+// prefill of 300 rows over 10 x 5000 keys, 32/8 heads, 400 workgroups 191,
+// 195; 200 rows over 8 x 3000, 32/2 heads, 224 workgroups 78, 68. (Without
+// grouping eight waves would be 256 rows of one head, whose waves finish at
+// different key tiles.)
 template <int D, bool CACHE, bool PAGED>
 hipError_t launch_fwd_p(const FwdArgs &a, hipStream_t stream) {
-  return a.hq / a.hkv >= 2 ? launch_fwd_w<D, CACHE, 8, PAGED>(a, stream)
-                           : launch_fwd_w<D, CACHE, 4, PAGED>(a, stream);
+  bool wide = false;
+  if (a.hq / a.hkv >= 2) {
+    const int hpw = gcd_int(a.hq / a.hkv, 8), rows = 8 / hpw * kQW;
+    const int64_t wgs = (int64_t)a.batch * (a.hq / hpw) * ((a.max_rows + rows - 1) / rows);
+    wide = CACHE ? wgs >= 288 : a.max_rows > 8192;
+  }
+  return wide ? launch_fwd_w<D, CACHE, 8, PAGED>(a, stream)
+              : launch_fwd_w<D, CACHE, 4, PAGED>(a, stream);
 }
 
 template <int D, bool CACHE>
