@@ -130,7 +130,10 @@ ism_status ism_visibility(const ism_segments *sg, int32_t *lim, int32_t *seer,
  * atomics. `deterministic` is reserved for a non-repeatable mode; today
  * both values run the repeatable path (a one-pass mode that adds dQ with
  * global atomics measured 2.2x slower on MI355X), so the result never
- * depends on it. Workspace: ISM_OP_BWD. */
+ * depends on it. Workspace: ISM_OP_BWD; on calls of few tokens that size has
+ * room for partial dK and dV that are added in order, and a workspace
+ * without it (down to 2 total_tokens * 4 + 2 total_tokens * hq * 8 bytes,
+ * each of the four rounded up to 256) runs them unshared. */
 ism_status ism_attn_bwd(const ism_segments *sg, const void *q, const void *k,
                         const void *v, const void *o, const float *lse,
                         const void *dout, float *dq, float *dk, float *dv,

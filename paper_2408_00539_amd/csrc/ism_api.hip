@@ -244,6 +244,17 @@ bool split_prefill(int32_t max_new, int32_t hq, int32_t hkv) {
   return (int64_t)max_new * (hq / hkv) <= 32;
 }
 
+// Workspace of the backward: what it needs, and the partial dK and dV of
+// calls whose key tiles are shared (left out if the caller's is smaller).
+size_t bwd_min_workspace(int32_t total, int32_t hq) {
+  return 2 * align_up((size_t)total * 4) + 2 * align_up((size_t)total * hq * 8);
+}
+size_t bwd_part_bytes(int32_t batch, int32_t total, int32_t hq, int32_t hkv, int32_t d) {
+  if (batch < 1 || hkv < 1 || hq < hkv) return 0;
+  const int parts = ism::bwd_dkv_parts(batch, total, hq, hkv);
+  return parts < 2 ? 0 : align_up((size_t)2 * parts * total * hkv * d * 4);
+}
+
 }  // namespace
 
 extern "C" size_t ism_attn_workspace_size(int32_t op, int32_t batch,
@@ -255,8 +266,8 @@ extern "C" size_t ism_attn_workspace_size(int32_t op, int32_t batch,
     case ISM_OP_FWD:
       return align_up((size_t)total_tokens * 4);
     case ISM_OP_BWD:
-      return 2 * align_up((size_t)total_tokens * 4) +
-             2 * align_up((size_t)total_tokens * hq * 8);
+      return bwd_min_workspace(total_tokens, hq) +
+             bwd_part_bytes(batch, total_tokens, hq, hkv, d);
     case ISM_OP_PREFILL_CACHED:
       return 0;
     case ISM_OP_DECODE: {
@@ -344,9 +355,9 @@ extern "C" ism_status ism_attn_bwd(const ism_segments *sg, const void *q,
   if (!q || !k || !v || !o || !lse || !dout || !dq || !dk || !dv)
     return fail(ISM_ERR_NULL, "q, k, v, o, lse, dout, dq, dk, dv are required");
   if ((st = check_heads(hq, hkv, d, scale))) return st;
-  const size_t need = ism_attn_workspace_size(ISM_OP_BWD, sg->batch, sg->total_tokens,
-                                              sg->max_seqlen, hq, hkv, d, 0);
+  const size_t need = bwd_min_workspace(sg->total_tokens, hq);
   if ((st = check_ws(ws, ws_bytes, need))) return st;
+  const size_t part_bytes = bwd_part_bytes(sg->batch, sg->total_tokens, hq, hkv, d);
   if ((st = check_device())) return st;
   if ((st = validate_segments(sg, (hipStream_t)stream))) return st;
 
@@ -363,6 +374,10 @@ extern "C" ism_status ism_attn_bwd(const ism_segments *sg, const void *q,
   ism::BwdArgs a{};
   a.q = q; a.k = k; a.v = v; a.o = o; a.dout = dout; a.lse = lse;
   a.dq = dq; a.dk = dk; a.dv = dv; a.lsex = lsex; a.deltax = deltax;
+  if (part_bytes && ws_bytes >= need + part_bytes) {
+    a.dkv_part = (float *)((char *)ws + need);
+    a.dkv_parts = ism::bwd_dkv_parts(sg->batch, sg->total_tokens, hq, hkv);
+  }
   a.cu_seqlens = sg->cu_seqlens; a.cu_segs = sg->cu_segs;
   a.seg_is_query = sg->seg_is_query; a.lim = lim; a.seer = seer;
   a.batch = sg->batch; a.num_segs = sg->num_segs; a.hq = hq; a.hkv = hkv;

@@ -19,6 +19,9 @@
 //     accumulates dV^T += dO^T P and dK^T += Q^T dS with P = exp(S - LSE),
 //     dS = P o (dP - delta), dP = dO V^T. Q and dO tiles are staged in LDS
 //     row-major; the products over rows read them through transposing reads.
+//     When the keys of a call make too few workgroups for the chip, several
+//     workgroups share a key tile's walk and a fourth kernel adds their
+//     partial dK and dV in order.
 // All products are bf16 MFMA 32x32x16 with fp32 accumulation; gradients are
 // written in fp32.
 #include "ism_common.h"
@@ -136,7 +139,7 @@ __device__ __forceinline__ void product_stream(Rd &&rd, Mm &&mm, Mid &&mid) {
 template <int D>
 __global__ void __launch_bounds__(512)
 __attribute__((amdgpu_waves_per_eu(ISM_DKV_WPE, ISM_DKV_WPE)))
-dkv_kernel(BwdArgs a, int ktiles) {
+dkv_kernel(BwdArgs a, int ktiles, int parts) {
   constexpr int NKS = D / 16, NDB = D / 32, RB = D * 2, LA = 3;
   constexpr int NRB = kBR / 32, NKK = kBR / 16;  // 32-row blocks, 16-row k steps
   __shared__ DkvSmem<D> sm;
@@ -149,10 +152,10 @@ dkv_kernel(BwdArgs a, int ktiles) {
   // (dialogue, KV head) groups run on one XCD each; early key tiles (the
   // longest row ranges) first.
   int group, kt;
-  if (!xcd_work_item((int)blockIdx.x, a.batch * a.hkv, ktiles, ISM_SCHED_CHUNK, false, group,
-                     kt))
+  if (!xcd_work_item((int)blockIdx.x, a.batch * a.hkv * parts, ktiles, ISM_SCHED_CHUNK, false,
+                     group, kt))
     return;
-  const int b = group / a.hkv, kvh = group % a.hkv;
+  const int part = group % parts, b = group / parts / a.hkv, kvh = group / parts % a.hkv;
   const int s = a.cu_seqlens[b], e = a.cu_seqlens[b + 1];
   const int c0 = s + kt * kKW;
   if (c0 >= e) return;
@@ -169,7 +172,9 @@ dkv_kernel(BwdArgs a, int ktiles) {
 
   const int rstart = a.seer[c0];
   const int nrt = (e - rstart + kBR - 1) / kBR;
-  const int iters = G * nrt;
+  // this workgroup's part of the (head, row tile) steps
+  const int it0 = (int)((int64_t)G * nrt * part / parts);
+  const int iters = (int)((int64_t)G * nrt * (part + 1) / parts) - it0;
   const int64_t rs = (int64_t)a.hq * D;
   DmaTile<D, kBR, 8> dma;
   dma.init(tid, rs);
@@ -177,7 +182,7 @@ dkv_kernel(BwdArgs a, int ktiles) {
   so.init(lane);
   // next tile to transfer: index, head, row tile; it goes to stage st, which
   // callers pass as a constant (nx % kDkvStages)
-  int nx = 0, nx_h = kvh * G, nx_rt = 0;
+  int nx = 0, nx_h = kvh * G + it0 / nrt, nx_rt = it0 % nrt;
   auto issue_next = [&](int st) __attribute__((always_inline)) {
     const int r0 = rstart + nx_rt * kBR;
     const int64_t base = ((int64_t)r0 * a.hq + nx_h) * D;
@@ -193,8 +198,8 @@ dkv_kernel(BwdArgs a, int ktiles) {
   };
   // B operands of this wave's products: K (P wave, for S) or V (dS wave,
   // for dP) of its 32 keys, lane <-> key, 8 head-dim values per k step;
-  // the first tile's transfer overlaps their loads (iters >= 1: the first
-  // key's own row sees it).
+  // the first tile's transfer overlaps their loads (none if the part is
+  // empty).
   bf16x8 bop[NKS];
   {
     const int kr = min(key, e - 1);
@@ -202,7 +207,7 @@ dkv_kernel(BwdArgs a, int ktiles) {
         (const bf16_t *)(pwave ? a.k : a.v) + ((int64_t)kr * a.hkv + kvh) * D + hf * 8;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) bop[ks] = *(const bf16x8 *)(src + ks * 16);
-    issue_next(0);
+    if (iters > 0) issue_next(0);
     wait_loads();  // also drains the first transfer
   }
   // B operand of the products that add a row's -lse / scale (P wave) or
@@ -416,7 +421,7 @@ dkv_kernel(BwdArgs a, int ktiles) {
   // keeps its accumulators in place. Each loop is unrolled by the ring depth
   // so that every tile, P and scalar buffer is a compile-time LDS offset.
   static_assert(kDkvStages == 3, "the role loops below are unrolled by three");
-  int rt = 0;
+  int rt = it0 % nrt;
   if (pwave) {
     auto step = [&](int it, auto stc) __attribute__((always_inline)) {
       constexpr int st = decltype(stc)::value;  // it % kDkvStages
@@ -454,11 +459,14 @@ dkv_kernel(BwdArgs a, int ktiles) {
     }
     // finish the last tile once its P is in LDS
     lds_barrier();
-    if (vis_prev) ds_dp((iters - 1) % kDkvStages, 0, T_{}, F_{});
+    if (vis_prev) ds_dp((iters + kDkvStages - 1) % kDkvStages, 0, T_{}, F_{});
   }
 
   if (!wactive || key >= e) return;
-  float *out = (pwave ? a.dv : a.dk) + ((int64_t)key * a.hkv + kvh) * D + hf * 4;
+  float *base = pwave ? a.dv : a.dk;
+  if (parts > 1)
+    base = a.dkv_part + (int64_t)((pwave ? parts : 0) + part) * a.total * a.hkv * D;
+  float *out = base + ((int64_t)key * a.hkv + kvh) * D + hf * 4;
   const float mul = pwave ? 1.f : a.scale;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -469,6 +477,20 @@ dkv_kernel(BwdArgs a, int ktiles) {
       for (int j = 0; j < 4; ++j) x[j] = acc[db][4 * i + j] * mul;
       *(f32x4 *)(out + db * 32 + 8 * i) = x;
     }
+}
+
+// dK and dV as the sums of their parts, in order (an HBM stream: parts + 1
+// passes over the two tensors).
+__global__ void __launch_bounds__(256)
+dkv_sum_kernel(const float *__restrict__ part, float *__restrict__ dk, float *__restrict__ dv,
+               int64_t n4, int parts) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= 2 * n4) return;
+  const bool second = i >= n4;
+  const f32x4 *p = (const f32x4 *)part + (second ? parts * n4 + (i - n4) : i);
+  f32x4 sum = p[0];
+  for (int s = 1; s < parts; ++s) sum += p[s * n4];
+  ((f32x4 *)(second ? dv : dk))[second ? i - n4 : i] = sum;
 }
 
 // ---------------------------------------------------------------- dQ
@@ -770,9 +792,15 @@ template <int D>
 hipError_t launch_bwd_t(const BwdArgs &a, hipStream_t stream) {
   hipError_t err = launch_dq<D, 4>(a, stream);
   if (err != hipSuccess) return err;
-  const int ktiles = (a.max_seqlen + kKW - 1) / kKW;
-  hipLaunchKernelGGL((dkv_kernel<D>), dim3((unsigned)xcd_grid((int64_t)a.batch * a.hkv, ktiles)),
-                     dim3(512), 0, stream, a, ktiles);
+  const int ktiles = (a.max_seqlen + kKW - 1) / kKW, parts = a.dkv_part ? a.dkv_parts : 1;
+  hipLaunchKernelGGL((dkv_kernel<D>),
+                     dim3((unsigned)xcd_grid((int64_t)a.batch * a.hkv * parts, ktiles)), dim3(512),
+                     0, stream, a, ktiles, parts);
+  err = hipGetLastError();
+  if (err != hipSuccess || parts == 1) return err;
+  const int64_t n4 = (int64_t)a.total * a.hkv * D / 4;
+  hipLaunchKernelGGL(dkv_sum_kernel, dim3((unsigned)((2 * n4 + 255) / 256)), dim3(256), 0, stream,
+                     a.dkv_part, a.dk, a.dv, n4, parts);
   return hipGetLastError();
 }
 

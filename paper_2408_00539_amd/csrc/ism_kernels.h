@@ -190,6 +190,8 @@ struct BwdArgs {
   // -lse / scale and -delta (delta = rowsum(dO * O)), each as the exact sum
   // of three bf16 values (plane 0: the first two, plane 1: the third and 0)
   uint32_t *lsex, *deltax;
+  float *dkv_part;          // [2, dkv_parts, T, hkv, d] partial dK and dV, or null
+  int32_t dkv_parts;        // workgroups that share a key tile's walk (bwd_dkv_parts)
   const int32_t *cu_seqlens;
   const int32_t *cu_segs;
   const uint8_t *seg_is_query;
@@ -199,6 +201,23 @@ struct BwdArgs {
   float scale, inv_scale;
   int32_t deterministic;
 };
+
+// Workgroups that share one key tile's walk in the dK/dV kernel, which runs
+// one workgroup per CU: as many as bring the call to about 512 (two rounds),
+// at least two steps of the average walk each. Fewer leave CUs idle behind
+// long walks; more pay for the sums. Measured training steps with 1, 256,
+// 512, 1024 workgroups (us): 2 x 4000 tokens, 16/2 heads 1027, 701, 641, 618;
+// 1 x 2000, 32/8 heads 284, 225, 212, 236; 1 x 8000, 8 heads (512 workgroups
+// by itself) 593, 594, 593, 650; 6 ragged up to 900, 16/4 heads, d 64: 105
+// unshared, 87 with four steps each, 82 with two.
+inline int bwd_dkv_parts(int batch, int total, int hq, int hkv) {
+  const int64_t wgs = (int64_t)hkv * (total / 128 + batch);
+  // a key tile sees half of its dialogue's 64-row tiles on average
+  const int64_t steps = (int64_t)(hq / hkv) * (total / batch) / 128;
+  int64_t parts = 512 / wgs;
+  if (parts > steps / 2) parts = steps / 2;
+  return parts < 2 ? 1 : parts > 8 ? 8 : (int)parts;
+}
 
 hipError_t launch_bwd_prep(const int32_t *cu_segs, const uint8_t *seg_is_query,
                            int32_t num_segs, int32_t total, int32_t *lim, int32_t *seer,

@@ -127,3 +127,47 @@ def test_mismatched_shapes_raise_before_launch():
                                    np.array([1, 0]))
     with pytest.raises(ValueError, match="total_tokens"):
         ops.bwd(q, k, v, o, lse, do, other)
+
+
+@pytest.mark.parametrize("hq,hkv,d,lens", [
+    (4, 1, 128, [1, 3, 2000]),        # 8 parts; fewer steps than parts in two dialogues
+    (16, 1, 64, [130, 64, 1, 700]),
+    (8, 8, 64, [1500, 65]),           # no grouping: the row tiles are shared out
+])
+def test_shared_key_tiles(hq, hkv, d, lens):
+    """Calls with few key tiles: several workgroups share a tile's walk and
+    their partial dK, dV are added, unless the workspace has no room for them.
+    Both against the oracle, the shared one twice with equal bits."""
+    import ctypes
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    segs = W.segments_from_lengths([W.alternating([n]) if n < 9 else
+                                    W.alternating([n // 3, n - n // 3]) for n in lens])
+    rng = np.random.default_rng(hq + d)
+    T = segs.total
+    q, k, v = _bits(rng, T, hq, d), _bits(rng, T, hkv, d), _bits(rng, T, hkv, d)
+    do, scale = _bits(rng, T, hq, d), 1 / np.sqrt(d)
+    size = ops.workspace_size(ops.ISM_OP_BWD, segs.batch, T, segs.max_seqlen, hq, hkv, d)
+    least = 2 * (-(-T * 4 // 256) * 256) + 2 * (-(-T * hq * 8 // 256) * 256)
+    assert size > least
+    announce("bwd shared key tiles", hq, hkv, d, lens)
+    one = _gpu_grads(segs, q, k, v, do, scale)
+    two = _gpu_grads(segs, q, k, v, do, scale)
+    for a, b in zip(one, two):
+        assert torch.equal(a, b)
+    S = ops.Segments.from_host(segs.cu_seqlens, segs.cu_segs, segs.seg_is_query)
+    dev = [dev_bf16(x) for x in (q, k, v)]
+    o, lse = ops.fwd(*dev, S, scale)
+    dout, ws = dev_bf16(do), torch.empty(least, dtype=torch.uint8, device="cuda")
+    plain = [torch.full_like(x, float("nan")) for x in one]
+    st = S.c_struct()
+    ptr = lambda x: ctypes.c_void_p(x.data_ptr())
+    assert ops.lib().ism_attn_bwd(
+        ctypes.byref(st), *map(ptr, (*dev, o, lse, dout, *plain)), hq, hkv, d, scale, 0, ptr(ws),
+        least, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    ref = oracle.bwd(f64(q), f64(k), f64(v), f64(do), segs.cu_seqlens, segs.cu_segs,
+                     segs.seg_is_query, scale)
+    for name, a, b, r in zip(("dQ", "dK", "dV"), one, plain, ref):
+        compare(name + " shared", host_f64(a), r)
+        compare(name + " unshared", host_f64(b), r)
