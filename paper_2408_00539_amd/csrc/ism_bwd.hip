@@ -143,6 +143,7 @@ dkv_kernel(BwdArgs a, int ktiles, int parts) {
   constexpr int NKS = D / 16, NDB = D / 32, RB = D * 2, LA = 3;
   constexpr int NRB = kBR / 32, NKK = kBR / 16;  // 32-row blocks, 16-row k steps
   __shared__ DkvSmem<D> sm;
+  __shared__ uint32_t tab[kMaxTableSegs + 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pair = wave & 3;
@@ -164,13 +165,25 @@ dkv_kernel(BwdArgs a, int ktiles, int parts) {
   const int G = a.hq / a.hkv;
   const float sl2 = a.scale * kLog2e;
 
-  // first rows that see the wave's first and last key, and this lane's key
-  const int seer_first = wactive ? a.seer[kw0] : e;
-  const int seer_last = (wactive && kw0 + 31 < e) ? a.seer[kw0 + 31] : e;
+  // first rows that see the wave's first and last key, this lane's key and
+  // the workgroup's first key
   const int key = kw0 + (lane & 31);
-  const int seer_k = key < e ? a.seer[key] : 0x7fffffff;
+  int seer_first, seer_last, seer_k, rstart;
+  if (a.seer) {
+    seer_first = wactive ? a.seer[kw0] : e;
+    seer_last = (wactive && kw0 + 31 < e) ? a.seer[kw0 + 31] : e;
+    seer_k = key < e ? a.seer[key] : 0x7fffffff;
+    rstart = a.seer[c0];
+  } else {
+    load_seg_table(tab, a.cu_segs, a.seg_is_query, a.num_segs, tid, 512);
+    lds_barrier();
+    const int seer = seg_seer(tab, a.num_segs, min(key, e - 1));
+    seer_first = wactive ? __builtin_amdgcn_readfirstlane(seer) : e;
+    seer_last = (wactive && kw0 + 31 < e) ? __builtin_amdgcn_readlane(seer, 31) : e;
+    seer_k = key < e ? seer : 0x7fffffff;
+    rstart = __builtin_amdgcn_readfirstlane(seg_seer(tab, a.num_segs, c0));
+  }
 
-  const int rstart = a.seer[c0];
   const int nrt = (e - rstart + kBR - 1) / kBR;
   // this workgroup's part of the (head, row tile) steps
   const int it0 = (int)((int64_t)G * nrt * part / parts);
@@ -514,6 +527,7 @@ __attribute__((amdgpu_waves_per_eu(ISM_DQ_WPE, ISM_DQ_WPE)))
 dq_kernel(BwdArgs a, int hpw, int tiles) {
   constexpr int NKS = D / 16, NDB = D / 32, RB = D * 2, LA = 3;
   __shared__ DqSmem<D> sm;
+  __shared__ uint32_t tab[kMaxTableSegs + 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
@@ -533,9 +547,7 @@ dq_kernel(BwdArgs a, int hpw, int tiles) {
   const int kvh = head0 / (a.hq / a.hkv);
   const int wq0 = q0 + (wave / hpw) * 32;
   const bool active = wq0 < e;
-  const int key_hi = a.lim[min(q0 + wg_rows, e) - 1];
-  const int wave_lo = a.lim[min(wq0, e - 1)];
-  const int wave_hi = active ? a.lim[min(wq0 + 32, e) - 1] : s - 1;
+  if (!a.lim) load_seg_table(tab, a.cu_segs, a.seg_is_query, a.num_segs, tid, NWV * 64);
   const float sl2 = a.scale * kLog2e;
 
   // The first K/V tile needs only the dialogue's key range in memory (keys
@@ -552,7 +564,19 @@ dq_kernel(BwdArgs a, int hpw, int tiles) {
   dma.issue(vt, rs, e - s, sm.v[0]);
 
   const int rc = min(wq0 + l32, e - 1);
-  const int lim_r = a.lim[rc];
+  int lim_r, key_hi, wave_lo, wave_hi;
+  if (a.lim) {
+    lim_r = a.lim[rc];
+    key_hi = a.lim[min(q0 + wg_rows, e) - 1];
+    wave_lo = a.lim[min(wq0, e - 1)];
+    wave_hi = active ? a.lim[min(wq0 + 32, e) - 1] : s - 1;
+  } else {
+    lds_barrier();  // the table
+    lim_r = seg_lim(tab, a.num_segs, rc);
+    key_hi = __builtin_amdgcn_readfirstlane(seg_lim(tab, a.num_segs, min(q0 + wg_rows, e) - 1));
+    wave_lo = __builtin_amdgcn_readfirstlane(lim_r);  // lane 0: the wave's first row
+    wave_hi = active ? __builtin_amdgcn_readlane(lim_r, 31) : s - 1;  // lane 31: its last
+  }
   const float lse_r = a.lse[(int64_t)head * a.total + rc];
   bf16x8 qf[NKS], df[NKS];
   float ndlt;  // -delta of the lane's row

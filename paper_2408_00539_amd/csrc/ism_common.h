@@ -471,4 +471,33 @@ __device__ __forceinline__ void rope_queries(bf16x8 (&qf)[D / 16], int hf, int p
   }
 }
 
+// The segment table of a short call in LDS, so that the attention kernels
+// form the Eq. 5 bounds themselves and no metadata launch runs first: the
+// first token of each segment with its query flag in bit 31.
+constexpr int kMaxTableSegs = 255;
+__device__ __forceinline__ void load_seg_table(uint32_t *tab, const int32_t *cu_segs,
+                                               const uint8_t *seg_is_query, int num_segs, int tid,
+                                               int threads) {
+  for (int i = tid; i <= num_segs; i += threads)
+    tab[i] = (uint32_t)cu_segs[i] | (i < num_segs && seg_is_query[i] ? 0x80000000u : 0u);
+}
+// The segment that holds token j: the largest g with a first token <= j.
+__device__ __forceinline__ int find_seg(const uint32_t *tab, int num_segs, int j) {
+  int lo = 0, hi = num_segs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if ((int)(tab[mid] & 0x7fffffffu) <= j) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+// Its inclusive last visible key, and the first row that sees key j.
+__device__ __forceinline__ int seg_lim(const uint32_t *tab, int num_segs, int j) {
+  const int g = find_seg(tab, num_segs, j);
+  return tab[g] >> 31 ? (int)(tab[g + 1] & 0x7fffffffu) - 1 : j;
+}
+__device__ __forceinline__ int seg_seer(const uint32_t *tab, int num_segs, int j) {
+  const uint32_t w = tab[find_seg(tab, num_segs, j)];
+  return w >> 31 ? (int)(w & 0x7fffffffu) : j;
+}
+
 }  // namespace ism

@@ -255,6 +255,7 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
   constexpr int NDB = D / 32;      // 32-wide d blocks of the output
   constexpr int NKS = D / 16;      // 16-deep k steps of Q K^T
   __shared__ FwdSmem<D> sm;
+  __shared__ uint32_t tab[CACHE ? 1 : kMaxTableSegs + 1];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
@@ -304,9 +305,14 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
     vbase = (const bf16_t *)a.v + off;
   } else {
     key_begin = s;
-    key_hi = a.lim[wg_last];
-    wave_lo = a.lim[min(wq0, e - 1)];
-    wave_hi = active ? a.lim[min(wq0 + kQW, e) - 1] : s - 1;
+    if (a.lim) {
+      key_hi = a.lim[wg_last];
+      wave_lo = a.lim[min(wq0, e - 1)];
+      wave_hi = active ? a.lim[min(wq0 + kQW, e) - 1] : s - 1;
+    } else {  // below, once the first transfers are on their way
+      load_seg_table(tab, a.cu_segs, a.seg_is_query, a.num_segs, tid, NWV * 64);
+      key_hi = wave_lo = wave_hi = s;
+    }
     kbase = (const bf16_t *)a.k + (int64_t)kvh * a.kv_head_stride;
     vbase = (const bf16_t *)a.v + (int64_t)kvh * a.kv_head_stride;
   }
@@ -343,9 +349,18 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
   // Per-lane query row (clamped into the dialogue; rows past e are computed
   // as copies of the last row and never stored).
   const int rc = min(wq0 + l32, e - 1);
-  const int lim_r = !CACHE          ? a.lim[rc]
-                    : a.cache_causal ? min(cache_c + (rc - s), key_hi)
-                                     : key_hi;
+  int lim_r;
+  if (CACHE) {
+    lim_r = a.cache_causal ? min(cache_c + (rc - s), key_hi) : key_hi;
+  } else if (a.lim) {
+    lim_r = a.lim[rc];
+  } else {
+    lds_barrier();  // the table
+    lim_r = seg_lim(tab, a.num_segs, rc);
+    key_hi = __builtin_amdgcn_readfirstlane(seg_lim(tab, a.num_segs, wg_last));
+    wave_lo = __builtin_amdgcn_readfirstlane(lim_r);  // lane 0: the wave's first row
+    wave_hi = active ? __builtin_amdgcn_readlane(lim_r, 31) : s - 1;  // lane 31: its last
+  }
   bf16x8 qf[NKS];
   {
     const bf16_t *qp = (const bf16_t *)a.q + ((int64_t)rc * a.hq + head) * D + hf * 8;

@@ -20,7 +20,11 @@ struct FwdArgs {
   void *o;
   float *lse;               // may be null
   const int32_t *cu_q;      // [batch+1] row ranges of q / o
-  const int32_t *lim;       // packed mode: [T] inclusive key bound per row
+  const int32_t *lim;       // packed mode: [T] inclusive key bound per row, or
+                            // null: formed from the segments below
+  const int32_t *cu_segs;
+  const uint8_t *seg_is_query;
+  int32_t num_segs;
   const int32_t *cache_len; // cache mode: [batch] cached tokens C_b
   int32_t batch;
   int32_t hq;
@@ -196,7 +200,8 @@ struct BwdArgs {
   const int32_t *cu_segs;
   const uint8_t *seg_is_query;
   const int32_t *lim;       // [T] inclusive key bound per row
-  const int32_t *seer;      // [T] first row that sees each key
+  const int32_t *seer;      // [T] first row that sees each key (both or none: null,
+                            // formed from the segments)
   int32_t batch, num_segs, hq, hkv, total, max_seqlen;
   float scale, inv_scale;
   int32_t deterministic;

@@ -171,3 +171,33 @@ def test_shared_key_tiles(hq, hkv, d, lens):
     for name, a, b, r in zip(("dQ", "dK", "dV"), one, plain, ref):
         compare(name + " shared", host_f64(a), r)
         compare(name + " unshared", host_f64(b), r)
+
+
+@pytest.mark.parametrize("segments", [255, 256])
+def test_segment_table_edges(segments):
+    """Short calls form their bounds from a table of up to 255 segments in
+    LDS, longer segment lists through the metadata launch: both against the
+    oracle, forward and backward, over segments of 1 to 9 tokens."""
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    rng = np.random.default_rng(segments)
+    n = rng.integers(1, 10, size=segments)
+    cut = segments // 3
+    segs = W.segments_from_lengths([W.alternating(n[:cut]),
+                                    W.alternating(n[cut:], first_is_query=False)])
+    hq, hkv, d, T = 4, 2, 64, segs.total
+    q, k, v = _bits(rng, T, hq, d), _bits(rng, T, hkv, d), _bits(rng, T, hkv, d)
+    do, scale = _bits(rng, T, hq, d), 1 / np.sqrt(d)
+    announce("segment table", segments, T)
+    S = ops.Segments.from_host(segs.cu_seqlens, segs.cu_segs, segs.seg_is_query)
+    dev = [dev_bf16(x) for x in (q, k, v)]
+    o, lse = ops.fwd(*dev, S, scale)
+    grads = ops.bwd(*dev, o, lse, dev_bf16(do), S, scale)
+    torch.cuda.synchronize()
+    args = (f64(q), f64(k), f64(v))
+    meta = (segs.cu_seqlens, segs.cu_segs, segs.seg_is_query, scale)
+    ro, rl = oracle.fwd(*args, *meta)
+    compare("O", host_f64(o), ro)
+    compare("LSE", host_f64(lse), rl)
+    for name, g, r in zip(("dQ", "dK", "dV"), grads, oracle.bwd(*args, f64(do), *meta)):
+        compare(name, host_f64(g), r)
