@@ -173,27 +173,33 @@ size_t decode_min_workspace(int32_t batch, int32_t max_len, int32_t hq, int32_t 
   return align_up((size_t)batch * hq * s * d * 4) + align_up((size_t)batch * hq * s * 2 * 4);
 }
 
-// The host part of a split-key launch (ism_split.hip): columns per workgroup
-// and how many units to make.
+// The host part of a split-key launch: the columns of a workgroup and how
+// many units to make. One-wave workgroups of 32 columns and 32-key tiles
+// (ism_split.hip, where the unit counts are measured), or the forward
+// kernel's of 128 columns and 64-key tiles. At least 128 or 256 keys per
+// chunk, at most 64 chunks.
 struct SplitPlan {
-  int32_t colw, col_groups, col_stride, budget, max_units, max_splits;
+  int32_t colw, col_groups, col_stride, budget, max_units, max_splits, tile_shift, min_tiles;
   // workspace of the partials and the plan (0: one chunk per dialogue)
   size_t part_bytes, ml_bytes, plan_bytes;
   size_t bytes() const { return part_bytes + ml_bytes + plan_bytes; }
 };
 
-constexpr int kSplitMinTiles = 4, kSplitUnits = 640, kSplitUnits64 = 960;  // measured in ism_split.hip
-SplitPlan split_plan(int32_t batch, int64_t total_rows, int32_t max_rows, int32_t hq, int32_t hkv, int32_t d,
-                     int64_t max_len, int32_t fixed, bool limited, size_t ws_bytes) {
+constexpr int kSplitUnits = 640, kSplitUnits64 = 960, kSplitUnits128 = 448;
+SplitPlan split_plan(int32_t batch, int64_t total_rows, int32_t max_rows, int32_t hq, int32_t hkv,
+                     int32_t d, int64_t max_len, int32_t fixed, bool limited, size_t ws_bytes) {
   SplitPlan p{};
   const int64_t cols = (int64_t)max_rows * (hq / hkv);
-  p.colw = 32;
-  p.col_groups = (int32_t)((cols + 31) / 32);
+  const bool one_wave = cols <= 32 || max_rows == 1;
+  p.colw = one_wave ? 32 : 128;
+  p.tile_shift = one_wave ? 5 : 6;
+  p.min_tiles = 4;
+  p.col_groups = (int32_t)((cols + p.colw - 1) / p.colw);
   p.col_stride = (int32_t)(cols < p.colw ? cols : p.colw);
-  p.budget = ((d == 64 ? kSplitUnits64 : kSplitUnits) + hkv - 1) / hkv;
-  const int64_t tiles = (max_len + ism::kSplitTile - 1) / ism::kSplitTile;
-  const int64_t most =
-      fixed > 0 ? fixed : (tiles + kSplitMinTiles - 1) / kSplitMinTiles;
+  const int target = !one_wave ? kSplitUnits128 : d == 64 ? kSplitUnits64 : kSplitUnits;
+  p.budget = (target + hkv - 1) / hkv;
+  const int64_t tiles = (max_len + (1 << p.tile_shift) - 1) >> p.tile_shift;
+  const int64_t most = fixed > 0 ? fixed : (tiles + p.min_tiles - 1) / p.min_tiles;
   p.max_splits = (int32_t)(most < 1 ? 1 : fixed <= 0 && most > 64 ? 64 : most);
   // column groups of all dialogues together, partials of one unit over all
   // KV heads
@@ -231,18 +237,30 @@ void apply_plan(ism::SplitArgs &a, const SplitPlan &p, int32_t fixed, void *ws) 
   a.colw = p.colw; a.col_groups = p.col_groups; a.col_stride = p.col_stride;
   a.budget = p.budget; a.inv_budget = 1.0001f / (float)p.budget;
   a.max_units = p.max_units; a.max_splits = p.max_splits;
-  a.min_tiles = kSplitMinTiles; a.fixed_splits = fixed;
+  a.min_tiles = p.min_tiles; a.tile_shift = p.tile_shift; a.fixed_splits = fixed;
   a.part_o = (float *)ws;
   a.part_ml = (float *)((char *)ws + p.part_bytes);
   a.plan = p.max_splits > 1 ? (int32_t *)((char *)ws + p.part_bytes + p.ml_bytes) : nullptr;
 }
 
-// Cached prefills that run split: the (row, query head) pairs of the longest
-// new segment that share a KV head fill at most one 32-column block, so that
-// the cache is streamed once. (Two blocks would stream it twice: the
-// row-tiled forward kernel shares its K/V tiles among eight waves.)
-bool split_prefill(int32_t max_new, int32_t hq, int32_t hkv) {
-  return (int64_t)max_new * (hq / hkv) <= 32;
+// How a cached prefill runs: kOneWave when the (row, query head) pairs of the
+// longest new segment that share a KV head fill at most one 32-column block,
+// so that the cache is streamed once (two blocks would stream it twice: the
+// row-tiled forward kernel shares its K/V tiles among four waves); else the
+// forward kernel, its key ranges split into about 448 units when its
+// workgroups leave most of the 512 that fit the chip unused. Measured
+// unsplit against split (us), by workgroups: 32 (8 ragged dialogues up to
+// 12000 keys, 16 rows, 32/2 heads) 172, 43; 32 (1 x 4000, 100 rows, 32/8) 64,
+// 31; 160 (10 x 3000, 50 rows, 32/8) 61, 55; 236 (8 ragged up to 3000, 200
+// rows, 32/2) 83, 114; 320 (20 ragged up to 4000, 60 rows, 32/8) 95, 120: the
+// partials of that many rows cost more than the idle workgroups.
+enum PrefillKind { kRowTiles, kRowTilesSplit, kOneWave };
+PrefillKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_new, int32_t hq,
+                         int32_t hkv) {
+  const int64_t g = hq / hkv;
+  if (max_new * g <= 32) return kOneWave;
+  const int64_t wgs = hkv * (total_new * g / 128 + batch);
+  return wgs < 192 ? kRowTilesSplit : kRowTiles;
 }
 
 // Short calls, whose kernels form the Eq. 5 bounds from the segments in LDS:
@@ -299,7 +317,7 @@ extern "C" size_t ism_attn_prefill_workspace_size(int32_t batch, int32_t total_n
                                                   int32_t max_new, int32_t hq, int32_t hkv,
                                                   int32_t d, int32_t cache_cap) {
   if (batch < 1 || total_new < 1 || max_new < 1 || hkv < 1 || hq < hkv || hq % hkv || d < 1 || cache_cap < 1 ||
-      !split_prefill(max_new, hq, hkv))
+      prefill_kind(batch, total_new, max_new, hq, hkv) == kRowTiles)
     return 0;
   const SplitPlan p = split_plan(batch, total_new, max_new, hq, hkv, d, cache_cap, 0, false, 0);
   return p.bytes();
@@ -479,9 +497,10 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
   const size_t split_need =
       ism_attn_prefill_workspace_size(batch, total_new, max_new, hq, hkv, d, cache_cap);
   // (no need: short caches, one chunk per dialogue)
-  const bool split =
-      split_prefill(max_new, hq, hkv) &&
-      (split_need == 0 || (ws && (uintptr_t)ws % kAlign == 0 && ws_bytes >= split_need));
+  const PrefillKind kind =
+      split_need == 0 || (ws && (uintptr_t)ws % kAlign == 0 && ws_bytes >= split_need)
+          ? prefill_kind(batch, total_new, max_new, hq, hkv)
+          : kRowTiles;
   if ((st = check_device())) return st;
   if ((st = validate_new_lengths(cu_seqlens_new, batch, total_new, max_new,
                                  (hipStream_t)stream)))
@@ -494,8 +513,8 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
     ae = ism::launch_cache_append_rope(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
                                        cache_seqlens, rp->pos1, rp->pos2, l2b, batch, max_new,
                                        hkv, d, cache_cap, s);
-  else if (split)
-    ;  // the split kernel appends
+  else if (kind == kOneWave)
+    ;  // its kernel appends
   else if (pg)
     ae = ism::launch_cache_append_paged(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
                                         cache_seqlens, pg->block_table, pg->max_pages,
@@ -504,8 +523,9 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
     ae = ism::launch_cache_append(k_new, v_new, k_cache, v_cache, cu_seqlens_new, cache_seqlens,
                                   batch, max_new, hkv, d, cache_cap, s);
   if ((st = hip_status(ae, "cache append launch"))) return st;
-  if (split) {
-    ism::SplitArgs a{};
+  ism::SplitArgs sp{};
+  if (kind != kRowTiles) {
+    ism::SplitArgs &a = sp;
     a.q = q_new; a.k_new = k_new; a.v_new = v_new; a.k_cache = k_cache; a.v_cache = v_cache;
     a.cu_new = cu_seqlens_new; a.cache_len = cache_seqlens; a.o = o; a.lse = lse;
     a.batch = batch; a.hq = hq; a.hkv = hkv; a.group = hq / hkv; a.cap = cache_cap;
@@ -525,7 +545,8 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
       a.rope_pos2 = rp->pos2;
       a.rope_log2_base = l2b;
     }
-    return hip_status(ism::launch_split(a, d, s), "cached prefill launch");
+    if (kind == kOneWave)
+      return hip_status(ism::launch_split(a, d, s), "cached prefill launch");
   }
   ism::FwdArgs a{};
   a.q = q_new; a.k = k_cache; a.v = v_cache; a.o = o; a.lse = lse;
@@ -551,7 +572,9 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
     a.rope_pos2 = rp->pos2;
     a.rope_log2_base = l2b;
   }
-  return hip_status(ism::launch_fwd(a, d, true, s), "cached prefill launch");
+  return hip_status(kind == kRowTilesSplit ? ism::launch_fwd_split(a, sp, d, s)
+                                           : ism::launch_fwd(a, d, true, s),
+                    "cached prefill launch");
 }
 
 }  // namespace

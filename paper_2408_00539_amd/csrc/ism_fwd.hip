@@ -3,13 +3,15 @@
 // accumulation. The same kernel serves the cached prefill of a new query
 // segment (Sec. 2.3), where every key of the concatenated cache is visible.
 //
-// Work decomposition. A workgroup (NWV = 4 or 8 waves) owns a row tile of one
-// dialogue and a set of query heads that share one KV head: with G = hq / hkv
-// query heads per KV head, hpw = gcd(G, NWV) heads run side by side (one per
-// wave column) so that the K/V tile staged in LDS serves all of them, and the
-// remaining NWV / hpw waves take consecutive 32-row blocks. Each wave
-// computes S^T = K Q^T for a 64-key tile (lane <-> query row, so the softmax
-// statistics of a row live in one lane pair), then O^T += V^T P^T.
+// Work decomposition. The (row, query head) pairs of a dialogue and a set of
+// query heads that share a KV head are the columns of S^T = K Q^T, row-major
+// (head innermost). A workgroup (NWV = 4 or 8 waves) owns 32 NWV consecutive
+// columns, 32 to a wave, so that the K/V tile staged in LDS serves every head
+// of the set, and a short segment fills whole waves (40 new rows with 4 heads
+// per KV head are 5 waves, where 32-row blocks per head took 8: 40 dialogues
+// of 2000 cached keys 119 -> 109 us). Each wave
+// computes S^T for a 64-key tile (lane <-> column, so the softmax statistics
+// of a row live in one lane pair), then O^T += V^T P^T.
 //
 // Mask handling. lim(j) is non-decreasing inside a dialogue, so a wave's
 // bounds are lim(first row) and lim(last row): key tiles past lim(last row)
@@ -18,6 +20,7 @@
 // in registers. No N x N mask exists anywhere.
 #include "ism_common.h"
 #include "ism_kernels.h"
+#include "ism_plan.h"
 
 namespace ism {
 
@@ -101,15 +104,22 @@ __device__ __forceinline__ float tile_max(const f32x16 (&s)[2]) {
   return pair_max(vmax(vmax(x[0], x[2]), vmax(x[1], x[3])));
 }
 
+// The reference max in log2 units. SPLIT: a row that has seen no key yet (an
+// answer row whose keys end before the chunk) has m = -inf and keeps l = 0.
+template <bool SPLIT>
+__device__ __forceinline__ float log2_max(float m, float sl2) {
+  return SPLIT && m == -INFINITY ? 0.f : m * sl2;
+}
+
 // Lazy online-softmax update: the reference max is only raised when a row's
 // tile max exceeds it by more than tau (2^8 in probability units); exact
 // either way since numerator and denominator share the reference max.
-template <int NDB>
+template <bool SPLIT, int NDB>
 __device__ __forceinline__ void raise_max(float mt, float sl2, float tau, float &m_run,
                                           float &l_run, f32x16 (&oacc)[NDB]) {
   if (__builtin_amdgcn_ballot_w64(mt > m_run + tau) != 0) {
     const float mnew = vmax(m_run, mt);
-    const float alpha = fast_exp2((m_run - mnew) * sl2);
+    const float alpha = SPLIT && mnew == -INFINITY ? 1.f : fast_exp2((m_run - mnew) * sl2);
     m_run = mnew;
     l_run *= alpha;
 #pragma unroll
@@ -248,10 +258,10 @@ __device__ __forceinline__ float step_block(const char *kl, const char *vl,
 // workgroup reads its K/V (verifying 8 drafted tokens per dialogue through
 // the cache ran 11 % faster; with several row tiles per group the same bit
 // cost the L2 sharing between them: the workload-3 prefill ran 22 % slower).
-template <int D, bool CACHE, int NWV, bool PAGED, bool NT>
+template <int D, bool CACHE, int NWV, bool PAGED, bool NT, bool SPLIT>
 __global__ void __launch_bounds__(NWV * 64)
 __attribute__((amdgpu_waves_per_eu(fwd_occupancy(D, NWV, PAGED), fwd_occupancy(D, NWV, PAGED))))
-fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
+fwd_kernel(FwdArgs a, int fold, int tiles, int chunk, SplitArgs sp) {
   constexpr int NDB = D / 32;      // 32-wide d blocks of the output
   constexpr int NKS = D / 16;      // 16-deep k steps of Q K^T
   __shared__ FwdSmem<D> sm;
@@ -261,23 +271,34 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
   const int l32 = lane & 31, hf = lane >> 5;
 
-  // Work item: (dialogue, head set) groups in XCD-aware chunks, longest row
-  // tile first inside each chunk.
-  const int hsets = a.hq / hpw;
-  int group, tile;
-  if (!xcd_work_item((int)blockIdx.x, a.batch * hsets, tiles, chunk, true, group, tile)) return;
-  const int b = group / hsets;
-  const int head0 = (group % hsets) * hpw;
-  const int wg_rows = (NWV / hpw) * kQW;
-  const int s = a.cu_q[b], e = a.cu_q[b + 1];
-  const int q0 = s + tile * wg_rows;
-  if (q0 >= e) return;
-
-  const int head = head0 + wave % hpw;
-  const int kvh = head0 / (a.hq / a.hkv);
-  const int wq0 = q0 + (wave / hpw) * kQW;
-  const bool active = wq0 < e;
-  const int wg_last = min(q0 + wg_rows, e) - 1;
+  // Work item: (dialogue, set of `fold` heads) groups in XCD-aware chunks,
+  // longest column tile first inside each chunk.
+  int b, head0, tile, kvh;
+  Unit u;  // SPLIT: the chunk of keys
+  if constexpr (SPLIT) {
+    if (!find_unit(sp, (int)blockIdx.x, lane, u)) return;
+    b = u.b;
+    kvh = u.kvh;
+    head0 = kvh * fold;
+    tile = __builtin_amdgcn_readfirstlane(u.cg);
+  } else {
+    const int hsets = a.hq / fold;
+    int group;
+    if (!xcd_work_item((int)blockIdx.x, a.batch * hsets, tiles, chunk, true, group, tile)) return;
+    b = group / hsets;
+    head0 = (group % hsets) * fold;
+    kvh = head0 / (a.hq / a.hkv);
+  }
+  const int s = a.cu_q[b];
+  const int e = SPLIT ? min(a.cu_q[b + 1], s + sp.max_rows) : a.cu_q[b + 1];
+  const uint32_t G = fold, ncol = (uint32_t)max(e - s, 0) * G;
+  const uint32_t c0 = (uint32_t)tile * (NWV * kQW), wc0 = c0 + wave * kQW;
+  if (c0 >= ncol) return;
+  const bool active = wc0 < ncol;
+  // rows of the workgroup's last column and of the wave's first and last
+  const int wg_last = s + (int)((min(c0 + NWV * kQW, ncol) - 1) / G);
+  const int wrow0 = s + (int)(min(wc0, ncol - 1) / G);
+  const int wrow1 = s + (int)((min(wc0 + kQW, ncol) - 1) / G);
 
   int key_begin, key_hi, wave_lo, wave_hi, cache_c = 0;
   bool oob = false;  // cache mode: C_b + L_b outside the cache (out of contract)
@@ -292,12 +313,21 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
     oob = cache_c < 0 || cache_c + (e - s) > slab_rows;
     if (a.cache_causal) {
       key_hi = max(min(cache_c + (wg_last - s) + 1, slab_rows) - 1, 0);
-      wave_lo = min(cache_c + (min(wq0, e - 1) - s), key_hi);
-      wave_hi = active ? min(cache_c + (min(wq0 + kQW, e) - 1 - s), key_hi) : -1;
+      wave_lo = min(cache_c + (wrow0 - s), key_hi);
+      wave_hi = active ? min(cache_c + (wrow1 - s), key_hi) : -1;
     } else {
       key_hi = max(min(cache_c + (e - s), slab_rows) - 1, 0);
       wave_lo = key_hi;
       wave_hi = active ? key_hi : -1;
+    }
+    if constexpr (SPLIT) {
+      // The chunk's keys. An answer segment's early rows may end before it:
+      // then one key, which exists, is staged and no wave uses it.
+      key_begin = __builtin_amdgcn_readfirstlane(u.tile0) * kBN;
+      key_hi = min(key_hi, key_begin + __builtin_amdgcn_readfirstlane(u.tiles) * kBN - 1);
+      key_hi = max(key_hi, key_begin);
+      wave_lo = min(wave_lo, key_hi);
+      wave_hi = min(wave_hi, key_hi);
     }
     const int64_t off =
         PAGED ? 0 : (int64_t)b * a.kv_seq_stride + (int64_t)kvh * a.kv_head_stride;
@@ -307,8 +337,8 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
     key_begin = s;
     if (a.lim) {
       key_hi = a.lim[wg_last];
-      wave_lo = a.lim[min(wq0, e - 1)];
-      wave_hi = active ? a.lim[min(wq0 + kQW, e) - 1] : s - 1;
+      wave_lo = a.lim[wrow0];
+      wave_hi = active ? a.lim[wrow1] : s - 1;
     } else {  // below, once the first transfers are on their way
       load_seg_table(tab, a.cu_segs, a.seg_is_query, a.num_segs, tid, NWV * 64);
       key_hi = wave_lo = wave_hi = s;
@@ -324,7 +354,8 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
   const int pg_max = a.max_pages, pg_num = a.num_pages, pg_size = a.page_size, nkv = a.hkv;
   auto tile_src = [&](const bf16_t *base, int t) __attribute__((always_inline)) {
     if constexpr (PAGED)
-      return base + paged_offset_uniform(btab, pg_max, pg_num, pg_size, nkv, D, b, kvh, t * kBN);
+      return base + paged_offset_uniform(btab, pg_max, pg_num, pg_size, nkv, D, b, kvh,
+                                         (SPLIT ? key_begin : 0) + t * kBN);
     else
       return base + (int64_t)key_begin * rs + (int64_t)t * (kBN * rs);
   };
@@ -346,9 +377,10 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
       dma.issue(PAGED ? tile_src(kbase, 1) : k0 + (int64_t)kBN * rs, rs, mem_rows - kBN,
                 sm.k[1]);
   }
-  // Per-lane query row (clamped into the dialogue; rows past e are computed
-  // as copies of the last row and never stored).
-  const int rc = min(wq0 + l32, e - 1);
+  // Per-lane column (columns past the last are computed as copies of it and
+  // never stored).
+  const uint32_t col = min(wc0 + l32, ncol - 1), crow = col / G;
+  const int rc = s + (int)crow, head = head0 + (int)(col - crow * G);
   int lim_r;
   if (CACHE) {
     lim_r = a.cache_causal ? min(cache_c + (rc - s), key_hi) : key_hi;
@@ -358,7 +390,7 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
     lds_barrier();  // the table
     lim_r = seg_lim(tab, a.num_segs, rc);
     key_hi = __builtin_amdgcn_readfirstlane(seg_lim(tab, a.num_segs, wg_last));
-    wave_lo = __builtin_amdgcn_readfirstlane(lim_r);  // lane 0: the wave's first row
+    wave_lo = __builtin_amdgcn_readfirstlane(lim_r);  // lane 0: the wave's first column
     wave_hi = active ? __builtin_amdgcn_readlane(lim_r, 31) : s - 1;  // lane 31: its last
   }
   bf16x8 qf[NKS];
@@ -387,7 +419,8 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
   // overlap. LDS holds K(t+1) and V(t) during step t while K(t+2) and V(t+1)
   // are in flight into the other halves of the double buffers.
   const int ntiles = (key_hi - key_begin) / kBN + 1;  // for the workgroup
-  const int nw = active ? (wave_hi - key_begin) / kBN + 1 : 0;  // this wave's
+  const int nw =  // this wave's (none if its rows end before a split chunk)
+      active && (!SPLIT || wave_hi >= key_begin) ? (wave_hi - key_begin) / kBN + 1 : 0;
   const int64_t tile_elems = (int64_t)kBN * rs;
   const bf16_t *kt = kbase + (int64_t)key_begin * rs;
   const bf16_t *vt = vbase + (int64_t)key_begin * rs;
@@ -401,7 +434,7 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
   if (nw > 0) {
     tile_scores<D>((const char *)sm.k[0], so, qf, sa);
     if (key_begin + kBN - 1 > wave_lo) tile_mask(sa, key_begin, hf, lim_r);
-    raise_max(tile_max(sa), sl2, tau, m_run, l_run, oacc);
+    raise_max<SPLIT>(tile_max(sa), sl2, tau, m_run, l_run, oacc);
   }
   lds_barrier();  // every wave is done with K(0) before K(2) overwrites it
 
@@ -438,23 +471,23 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
     };
     if (t < nw) {
       float mt;
-      l_run += step_block<D, LAST, !PAGED>(kl, vl, so, qf, cur, nxt, oacc, sl2, m_run * sl2, mt,
-                                           hook);
+      l_run += step_block<D, LAST, !PAGED>(kl, vl, so, qf, cur, nxt, oacc, sl2,
+                                           log2_max<SPLIT>(m_run, sl2), mt, hook);
       if (!LAST && t + 1 < nw) {
         if (c0 + 2 * kBN - 1 > wave_lo) {  // S(t+1) crosses some row's bound
           tile_mask(nxt, c0 + kBN, hf, lim_r);
           mt = tile_max(nxt);
         }
-        raise_max(mt, sl2, tau, m_run, l_run, oacc);
+        raise_max<SPLIT>(mt, sl2, tau, m_run, l_run, oacc);
       }
     }
     if (!LAST) {
       kt += tile_elems;
       vt += tile_elems;
       if constexpr (PAGED) {  // K(t+3) and V(t+2), re-based at page starts
-        const int tpp = pg_size / kBN;
-        pk2 = (t + 3) % tpp ? pk2 + tile_elems : tile_src(kbase, min(t + 3, ntiles - 1));
-        pv1 = (t + 2) % tpp ? pv1 + tile_elems : tile_src(vbase, min(t + 2, ntiles - 1));
+        const int tpp = pg_size / kBN, ta = (SPLIT ? key_begin / kBN : 0) + t;
+        pk2 = (ta + 3) % tpp ? pk2 + tile_elems : tile_src(kbase, min(t + 3, ntiles - 1));
+        pv1 = (ta + 2) % tpp ? pv1 + tile_elems : tile_src(vbase, min(t + 2, ntiles - 1));
       }
     }
     wait_vmem();
@@ -480,10 +513,29 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
 
   if (!active) return;
   const float lt = pair_sum(l_run);
-  const int row = wq0 + l32;
-  if (row >= e) return;
+  // the lane's row and head again (kept over the loop they would cost
+  // registers that d = 64 at three waves per SIMD does not have)
+  int ln;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+  const uint32_t ocol = wc0 + (ln & 31), orow = ocol / G;
+  if (ocol >= ncol) return;
+  const int row = s + (int)orow, ohead = head0 + (int)(ocol - orow * G);
+  if constexpr (SPLIT) {
+    if (u.n > 1) {  // partials, merged by the split-key kernel's combine
+      const int64_t pi = (int64_t)u.slot * sp.col_stride + (ocol - c0);
+      float *po = sp.part_o + pi * D + hf * 4;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *(f32x4 *)(po + db * 32 + 8 * i) = f32x4{oacc[db][4 * i], oacc[db][4 * i + 1],
+                                                   oacc[db][4 * i + 2], oacc[db][4 * i + 3]};
+      if (hf == 0) *(f32x2 *)(sp.part_ml + pi * 2) = f32x2{m_run * sl2, lt};
+      return;
+    }
+  }
   const float inv = oob ? __builtin_nanf("") : 1.f / lt;
-  bf16_t *op = (bf16_t *)a.o + ((int64_t)row * a.hq + head) * D + hf * 4;
+  bf16_t *op = (bf16_t *)a.o + ((int64_t)row * a.hq + ohead) * D + hf * 4;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -494,7 +546,7 @@ fwd_kernel(FwdArgs a, int hpw, int tiles, int chunk) {
       *(u32x2 *)(op + db * 32 + 8 * i) = w;
     }
   if (a.lse && hf == 0)
-    a.lse[(int64_t)head * a.total_q + row] = oob ? __builtin_nanf("") : m_run * a.scale + logf(lt);
+    a.lse[(int64_t)ohead * a.total_q + row] = oob ? __builtin_nanf("") : m_run * a.scale + logf(lt);
 }
 
 int gcd_int(int x, int y) {
@@ -502,48 +554,56 @@ int gcd_int(int x, int y) {
   return x;
 }
 
+// Query heads folded into a workgroup's columns: the whole group in cache
+// mode, where rows are few; packed, the part of it that fills whole waves (a
+// group of 3 as one set ran 12 ragged dialogues up to 900 tokens, 24/8 heads,
+// in 67 us instead of 60).
+int fold_of(const FwdArgs &a, bool cache, int waves) {
+  const int g = a.hq / a.hkv;
+  return cache ? g : gcd_int(g, waves);
+}
+
+int64_t column_tiles(const FwdArgs &a, int fold, int waves) {
+  const int64_t w = waves * kQW;
+  return ((int64_t)a.max_rows * fold + w - 1) / w;
+}
+
 template <int D, bool CACHE, int NWV, bool PAGED>
 hipError_t launch_fwd_w(const FwdArgs &a, hipStream_t stream) {
-  const int hpw = gcd_int(a.hq / a.hkv, NWV);
-  const int wg_rows = (NWV / hpw) * kQW;
-  const int tiles = (a.max_rows + wg_rows - 1) / wg_rows;
-  const int64_t groups = (int64_t)a.batch * (a.hq / hpw);
+  const int fold = fold_of(a, CACHE, NWV);
+  const int tiles = (int)column_tiles(a, fold, NWV);
+  const int64_t groups = (int64_t)a.batch * (a.hq / fold);
   if (groups * tiles == 0) return hipSuccess;
   const dim3 grid((unsigned)xcd_grid(groups, tiles));
   if constexpr (CACHE) {
     if (tiles == 1) {
-      hipLaunchKernelGGL((fwd_kernel<D, true, NWV, PAGED, true>), grid, dim3(NWV * 64), 0,
-                         stream, a, hpw, tiles, ISM_SCHED_CHUNK);
+      hipLaunchKernelGGL((fwd_kernel<D, true, NWV, PAGED, true, false>), grid, dim3(NWV * 64), 0,
+                         stream, a, fold, tiles, ISM_SCHED_CHUNK, SplitArgs{});
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((fwd_kernel<D, CACHE, NWV, PAGED, false>), grid, dim3(NWV * 64), 0,
-                     stream, a, hpw, tiles, ISM_SCHED_CHUNK);
+  hipLaunchKernelGGL((fwd_kernel<D, CACHE, NWV, PAGED, false, false>), grid, dim3(NWV * 64), 0,
+                     stream, a, fold, tiles, ISM_SCHED_CHUNK, SplitArgs{});
   return hipGetLastError();
 }
 
 // Four-wave workgroups, two (three at d = 64) to a CU, so that one's prologue
 // and last steps run beside another's products. Eight-wave workgroups stage
 // each K/V tile for twice the columns, half the transfers per product, but
-// are alone on their CU: with grouped KV heads (the heads of a group share
-// every tile) they still win on long key loops, where the prologue is small,
-// and on cached prefills that fill the chip, whose K/V come from HBM.
-// Measured, 8 waves against 4 (us): packed 32/8 heads 2 x 16384 3733, 3752;
-// 6 ragged dialogues up to 3000 348, 330; 24/8 heads 12 x 900 74, 60; cached
-// prefill of 300 rows over 10 x 5000 keys, 32/8 heads, 400 workgroups 191,
-// 195; 200 rows over 8 x 3000, 32/2 heads, 224 workgroups 78, 68. (Without
-// grouping eight waves would be 256 rows of one head, whose waves finish at
-// different key tiles.)
+// are alone on their CU: packed with grouped KV heads they still win on long
+// key loops, where the prologue is small. Measured, 8 waves against 4 (us):
+// packed 32/8 heads 2 x 16384 3733, 3752; 6 ragged dialogues up to 3000 348,
+// 330; 24/8 heads 12 x 900 74, 60; cached, 40 new rows over 40 x 2000 keys,
+// 32/8 heads 124, 117; 12 rows over 40 ragged up to 3000, 64/8 heads 139, 91.
+// (Without grouping eight waves would be 256 rows of one head, whose waves
+// finish at different key tiles. In cache mode a ring of four K/V tiles for
+// eight waves alone on their CU measured 124 on the first of these.)
 template <int D, bool CACHE, bool PAGED>
 hipError_t launch_fwd_p(const FwdArgs &a, hipStream_t stream) {
-  bool wide = false;
-  if (a.hq / a.hkv >= 2) {
-    const int hpw = gcd_int(a.hq / a.hkv, 8), rows = 8 / hpw * kQW;
-    const int64_t wgs = (int64_t)a.batch * (a.hq / hpw) * ((a.max_rows + rows - 1) / rows);
-    wide = CACHE ? wgs >= 288 : a.max_rows > 8192;
+  if constexpr (!CACHE) {
+    if (a.hq / a.hkv >= 2 && a.max_rows > 8192) return launch_fwd_w<D, false, 8, false>(a, stream);
   }
-  return wide ? launch_fwd_w<D, CACHE, 8, PAGED>(a, stream)
-              : launch_fwd_w<D, CACHE, 4, PAGED>(a, stream);
+  return launch_fwd_w<D, CACHE, 4, PAGED>(a, stream);
 }
 
 template <int D, bool CACHE>
@@ -552,7 +612,28 @@ hipError_t launch_fwd_t(const FwdArgs &a, hipStream_t stream) {
   return launch_fwd_p<D, CACHE, false>(a, stream);
 }
 
+template <int D, bool PAGED>
+hipError_t launch_fwd_split_p(const FwdArgs &a, const SplitArgs &sp, hipStream_t stream) {
+  const dim3 grid((unsigned)(((int64_t)sp.max_units * a.hkv + 7) / 8 * 8));
+  if (sp.col_groups == 1)
+    hipLaunchKernelGGL((fwd_kernel<D, true, 4, PAGED, true, true>), grid, dim3(256), 0, stream, a,
+                       a.hq / a.hkv, 0, 0, sp);
+  else
+    hipLaunchKernelGGL((fwd_kernel<D, true, 4, PAGED, false, true>), grid, dim3(256), 0, stream, a,
+                       a.hq / a.hkv, 0, 0, sp);
+  const hipError_t err = hipGetLastError();
+  return err == hipSuccess && sp.max_splits > 1 ? launch_split_combine(sp, D, stream) : err;
+}
+
 }  // namespace
+
+hipError_t launch_fwd_split(const FwdArgs &a, const SplitArgs &sp, int d, hipStream_t stream) {
+  if (d == 128) return a.block_table ? launch_fwd_split_p<128, true>(a, sp, stream)
+                                     : launch_fwd_split_p<128, false>(a, sp, stream);
+  if (d == 64) return a.block_table ? launch_fwd_split_p<64, true>(a, sp, stream)
+                                    : launch_fwd_split_p<64, false>(a, sp, stream);
+  return hipErrorInvalidValue;
+}
 
 hipError_t launch_fwd(const FwdArgs &a, int d, bool cache_mode,
                       hipStream_t stream) {

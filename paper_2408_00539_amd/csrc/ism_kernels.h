@@ -151,7 +151,6 @@ inline int decode_heads_per_set(int batch, int hq, int hkv) {
 
 // Attention of the new rows of each dialogue over its cache with the keys
 // split over workgroups (ism_split.hip); the host part of its plan.
-constexpr int kSplitTile = 32;  // keys per tile
 struct SplitArgs {
   const void *q;             // [total_q, hq, d]
   const void *k_new, *v_new; // [total_q, hkv, d]
@@ -167,13 +166,14 @@ struct SplitArgs {
   float scale;
   int32_t causal;            // row r sees keys [0, C_b + r], else all
   int32_t append;            // read new rows from the input, store them into the cache
-  int32_t colw;              // columns (row, head) per workgroup: 32 per wave
+  int32_t colw;              // columns (row, head) per workgroup: 32, or 128 (row-tiled)
   int32_t col_groups;        // column groups of the longest dialogue
   int32_t col_stride;        // columns per partials slot
   int32_t budget;            // units (chunk, column group) per KV head to aim at
   float inv_budget;          // 1 / budget, rounded up a little
   int32_t max_units;         // bound of the units per KV head
   int32_t max_splits;        // chunks per dialogue at most
+  int32_t tile_shift;        // log2 of the keys per tile (32 or 64)
   int32_t min_tiles;         // tiles per chunk at least (automatic plan)
   int32_t fixed_splits;      // > 0: that many chunks per dialogue
   // paged cache (see FwdArgs)
@@ -185,6 +185,10 @@ struct SplitArgs {
 };
 
 hipError_t launch_split(const SplitArgs &a, int d, hipStream_t stream);
+hipError_t launch_split_combine(const SplitArgs &a, int d, hipStream_t stream);
+// The forward kernel in cache mode over the units of such a plan (128
+// columns, 64-key tiles), for longer segments that do not fill the chip.
+hipError_t launch_fwd_split(const FwdArgs &a, const SplitArgs &sp, int d, hipStream_t stream);
 
 struct BwdArgs {
   const void *q, *k, *v, *o, *dout;

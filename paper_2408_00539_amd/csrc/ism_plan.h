@@ -11,8 +11,6 @@ namespace ism {
 
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kT = kSplitTile;  // keys per tile
-
 // A dialogue's extent. For an out-of-contract length (oob) the new rows that
 // fall inside the cache are appended all the same, and the outputs become
 // NaN.
@@ -48,13 +46,13 @@ __device__ __forceinline__ RawLen raw_len(const SplitArgs &a, int b) {
   return r;
 }
 
-__device__ __forceinline__ int tiles_of(const Extent &x) {
-  return x.rows > 0 ? (x.keys + kT - 1) / kT : 0;
+__device__ __forceinline__ int tiles_of(const SplitArgs &a, const Extent &x) {
+  return x.rows > 0 ? ((x.keys - 1) >> a.tile_shift) + 1 : 0;
 }
 
 // Column groups (workgroups per chunk and KV head) of `rows` new rows.
 __device__ __forceinline__ int groups_of(const SplitArgs &a, int rows) {
-  return min((int)(((int64_t)rows * a.group + a.colw - 1) / a.colw), a.col_groups);
+  return min((int)(((int64_t)rows * a.group + a.colw - 1) >> (a.colw == 32 ? 5 : 7)), a.col_groups);
 }
 
 // a / b (a >= 0, b >= 1) through the hardware reciprocal: exact for
@@ -129,7 +127,7 @@ __device__ __forceinline__ bool find_unit(const SplitArgs &a, int bid, int lane,
     if (b < a.batch) {
       r = raw_len(a, b);
       const Extent x = extent_from(a, r.r0, r.rows, r.cached);
-      t = tiles_of(x);
+      t = tiles_of(a, x);
       g = groups_of(a, x.rows);
     }
   };
@@ -155,7 +153,8 @@ __device__ __forceinline__ bool find_unit(const SplitArgs &a, int bid, int lane,
     load(b0 + lane);
     all += __builtin_amdgcn_readlane(wave_scan(chunks_of(a, t, lc) * g), 63);
   }
-  const int units = all * a.hkv, per_xcd = (units + 7) >> 3;
+  // (never more than the host made room for, whatever the length arrays say)
+  const int units = min(all, a.max_units) * a.hkv, per_xcd = (units + 7) >> 3;
   const int i = bid >> 3, flat = (bid & 7) * per_xcd + i;
   if (i >= per_xcd || flat >= units) return false;
   int base = 0, b0 = 0;

@@ -38,7 +38,8 @@ namespace ism {
 
 namespace {
 
-constexpr int R = 2;  // ring of K/V tiles
+constexpr int kT = 32;  // keys per tile
+constexpr int R = 2;    // ring of K/V tiles
 template <int D>
 struct SplitSmem {
   bf16_t kv[R][2][kT * D];
@@ -266,7 +267,7 @@ split_attn_kernel(SplitArgs a) {
 template <int D>
 __global__ void __launch_bounds__(256)
 split_combine_kernel(SplitArgs a) {
-  constexpr int E = D / 64, U = 16;  // values per lane, chunks in flight
+  constexpr int E = D / 64, U = 16, F = 8;  // values per lane, chunks in flight
   typedef float vecE __attribute__((ext_vector_type(E)));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -280,13 +281,32 @@ split_combine_kernel(SplitArgs a) {
   for (int col = (int)blockIdx.x * 4 + wave; col < ncol; col += (int)gridDim.x * 4) {
     const int row = col / a.hq, head = col - row * a.hq, kvh = head / a.group;
     const int idx = row * a.group + (head - kvh * a.group);
-    const int cg = idx / a.colw;
+    const int cg = idx >> (a.colw == 32 ? 5 : 7);
     const int64_t p0 =
         ((int64_t)pl[1] + kvh * groups + cg) * a.col_stride + (idx - cg * a.colw);
     float mx = -INFINITY, lt = 0.f, acc[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[e] = 0.f;
-    for (int s0 = 0; s0 < n; s0 += 64) {
+    if (n <= F) {  // every lane forms the weights itself: one round of loads
+      f32x2 ml[F];
+      vecE v[F];
+#pragma unroll
+      for (int s = 0; s < F; ++s) {
+        ml[s] = s < n ? *(const f32x2 *)(a.part_ml + (p0 + s * step) * 2) : f32x2{-INFINITY, 0.f};
+        v[s] = s < n ? *(const vecE *)(a.part_o + (p0 + s * step) * D + lane * E) : vecE{};
+      }
+#pragma unroll
+      for (int s = 0; s < F; ++s) mx = fmaxf(mx, ml[s][0]);
+      const float mref = mx == -INFINITY ? 0.f : mx;
+#pragma unroll
+      for (int s = 0; s < F; ++s) {
+        const float w = fast_exp2(ml[s][0] - mref);
+        lt = fmaf(ml[s][1], w, lt);
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = fmaf(v[s][e], w, acc[e]);
+      }
+    }
+    for (int s0 = 0; s0 < n && n > F; s0 += 64) {
       // (more than 64 chunks: rescale what the earlier ones gave)
       const int nn = min(64, n - s0);
       f32x2 ml = f32x2{-INFINITY, 0.f};
@@ -315,8 +335,10 @@ split_combine_kernel(SplitArgs a) {
         }
       }
     }
+    if (n > F) {
 #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) lt += __shfl_xor(lt, s);
+      for (int s = 32; s >= 1; s >>= 1) lt += __shfl_xor(lt, s);
+    }
     bf16_t *op = (bf16_t *)a.o + ((int64_t)(x.r0 + row) * a.hq + head) * D + lane * E;
     if (x.oob) lt = __builtin_nanf("");
     if constexpr (E == 2) *(uint32_t *)op = pack_bf16x2(acc[0] / lt, acc[1] / lt);
@@ -330,15 +352,19 @@ template <int D, bool PAGED>
 hipError_t launch_split_p(const SplitArgs &a, hipStream_t stream) {
   const dim3 grid((unsigned)(((int64_t)a.max_units * a.hkv + 7) / 8 * 8));
   hipLaunchKernelGGL((split_attn_kernel<D, PAGED>), grid, dim3(64), 0, stream, a);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess || a.max_splits == 1) return err;
-  const int64_t cols = (int64_t)a.max_rows * a.hq;
-  const dim3 cgrid((unsigned)((cols + 3) / 4 < 1024 ? (cols + 3) / 4 : 1024), a.batch);
-  hipLaunchKernelGGL((split_combine_kernel<D>), cgrid, dim3(256), 0, stream, a);
-  return hipGetLastError();
+  const hipError_t err = hipGetLastError();
+  return err == hipSuccess && a.max_splits > 1 ? launch_split_combine(a, D, stream) : err;
 }
 
 }  // namespace
+
+hipError_t launch_split_combine(const SplitArgs &a, int d, hipStream_t stream) {
+  const int64_t wgs = ((int64_t)a.max_rows * a.hq + 3) / 4;
+  const dim3 grid((unsigned)(wgs < 1024 ? wgs : 1024), a.batch);
+  if (d == 128) hipLaunchKernelGGL(split_combine_kernel<128>, grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(split_combine_kernel<64>, grid, dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_split(const SplitArgs &a, int d, hipStream_t stream) {
   if (d == 128) return a.block_table ? launch_split_p<128, true>(a, stream)

@@ -1,5 +1,5 @@
-"""GPU parity of the split-key cache kernel (ism_split.hip) where its plan and
-its tiles can go wrong: column counts (new rows x query heads per KV head)
+"""GPU parity of the split-key cache kernels (ism_split.hip, and the forward
+kernel over the same plan) where the plan and the tiles can go wrong: column counts (new rows x query heads per KV head)
 around one 32-column block, histories at the edges of the 32-key tiles, more
 dialogues than lanes of the planning wave, dialogues without new rows, ragged
 lengths that are cut into one to many chunks, workspaces from none to full,
@@ -31,10 +31,16 @@ def _hist(rng, batch, longest):
 @pytest.mark.parametrize("batch,longest,hq,hkv,d,new,is_query", [
     (11, 2100, 8, 2, 128, 8, False),    # 32 columns, many chunks
     (11, 2100, 3, 1, 64, 10, False),    # 30 columns, group of 3
-    (11, 700, 8, 2, 128, 9, True),      # 36 columns: the row-tiled kernel
+    (11, 700, 8, 2, 128, 9, True),      # 36 columns: row-tiled
     (5, 130, 1, 1, 64, 32, False),      # no grouping
     (70, 300, 4, 1, 128, 4, False),     # more dialogues than lanes
     (130, 90, 2, 2, 64, 3, True),
+    # the row-tiled kernel over split key ranges: chunks that some or all rows
+    # of a workgroup end before, several column groups, heads of a group of 3
+    (4, 2100, 4, 1, 128, 150, False),
+    (5, 1300, 2, 2, 64, 200, False),
+    (11, 900, 16, 1, 64, 40, True),
+    (3, 5000, 3, 1, 128, 33, False),
 ])
 def test_ragged_chunks(batch, longest, hq, hkv, d, new, is_query):
     torch = torch_cuda()
