@@ -186,6 +186,15 @@ struct SplitPlan {
 };
 
 constexpr int kSplitUnits = 640, kSplitUnits64 = 960, kSplitUnits128 = 448;
+// From this many (dialogue, KV head, column group) workgroups on (1280 one-wave
+// workgroups fit the chip), a one-wave launch keeps every dialogue whole and
+// needs no plan, whose scans over many dialogues every workgroup would repeat.
+// Measured with the plan and without (us): decode, 32/8 heads, 256 ragged
+// dialogues up to 1000 keys 106.3, 101.6; 1000: 404, 347; 2000: 1080, 845; 8
+// drafted rows over 300 ragged up to 800 keys 128, 114; 64/8 heads, d 64, 256
+// x 300 keys 34.9, 28.1. Below it, splitting the long dialogues of a ragged
+// batch is worth the plan.
+constexpr int kSplitDirect = 2048;
 SplitPlan split_plan(int32_t batch, int64_t total_rows, int32_t max_rows, int32_t hq, int32_t hkv,
                      int32_t d, int64_t max_len, int32_t fixed, bool limited, size_t ws_bytes) {
   SplitPlan p{};
@@ -201,6 +210,8 @@ SplitPlan split_plan(int32_t batch, int64_t total_rows, int32_t max_rows, int32_
   const int64_t tiles = (max_len + (1 << p.tile_shift) - 1) >> p.tile_shift;
   const int64_t most = fixed > 0 ? fixed : (tiles + p.min_tiles - 1) / p.min_tiles;
   p.max_splits = (int32_t)(most < 1 ? 1 : fixed <= 0 && most > 64 ? 64 : most);
+  if (one_wave && fixed <= 0 && (int64_t)batch * hkv * p.col_groups >= kSplitDirect)
+    p.max_splits = 1;
   // column groups of all dialogues together, partials of one unit over all
   // KV heads
   const int64_t by_rows = total_rows * (hq / hkv) / p.colw + batch, groups = p.col_groups;

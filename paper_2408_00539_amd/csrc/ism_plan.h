@@ -119,6 +119,25 @@ struct Unit {
 // contiguous eighth of the units and the column groups that read the same
 // chunk share its L2.
 __device__ __forceinline__ bool find_unit(const SplitArgs &a, int bid, int lane, Unit &u) {
+  if (a.max_splits == 1 && a.colw == 32) {
+    // One chunk per dialogue and the same column groups in each (a one-wave
+    // launch has several only with one row per dialogue): no plan is needed.
+    const int units = a.batch * a.col_groups * a.hkv, per_xcd = (units + 7) >> 3;
+    const int i = bid >> 3, flat = (bid & 7) * per_xcd + i;
+    if (i >= per_xcd || flat >= units) return false;
+    u.b = __builtin_amdgcn_readfirstlane(quot(flat, a.col_groups * a.hkv));
+    const int k = flat - u.b * a.col_groups * a.hkv;
+    u.kvh = __builtin_amdgcn_readfirstlane(quot(k, a.col_groups));
+    u.cg = k - u.kvh * a.col_groups;
+    const RawLen r = raw_len(a, u.b);
+    u.x = extent_from(a, r.r0, r.rows, r.cached);
+    u.x.keys = __builtin_amdgcn_readfirstlane(u.x.keys);
+    u.split = u.tile0 = 0;
+    u.n = 1;
+    u.slot = flat;
+    u.tiles = __builtin_amdgcn_readfirstlane(tiles_of(a, u.x));
+    return u.tiles > 0;
+  }
   RawLen r{0, 0, 0};  // dialogue `lane` (kept: most batches fit one wave)
   int t = 0, g = 0;
   auto load = [&](int b) __attribute__((always_inline)) {

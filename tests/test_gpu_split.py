@@ -35,6 +35,7 @@ def _hist(rng, batch, longest):
     (5, 130, 1, 1, 64, 32, False),      # no grouping
     (70, 300, 4, 1, 128, 4, False),     # more dialogues than lanes
     (130, 90, 2, 2, 64, 3, True),
+    (260, 70, 16, 8, 64, 3, False),     # 2080 workgroups: whole dialogues, no plan
     # the row-tiled kernel over split key ranges: chunks that some or all rows
     # of a workgroup end before, several column groups, heads of a group of 3
     (4, 2100, 4, 1, 128, 150, False),
