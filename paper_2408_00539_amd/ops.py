@@ -151,7 +151,7 @@ def _need(t, name, dtype, shape=None):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape}")
 
 
-@functools.lru_cache(maxsize=256)
+@functools.lru_cache(maxsize=256, typed=True)
 def workspace_size(op, batch=0, total_tokens=0, max_seqlen=0, hq=0, hkv=0,
                    d=0, num_splits=0):
     return int(lib().ism_attn_workspace_size(op, batch, total_tokens,
@@ -159,7 +159,7 @@ def workspace_size(op, batch=0, total_tokens=0, max_seqlen=0, hq=0, hkv=0,
                                              num_splits))
 
 
-@functools.lru_cache(maxsize=256)
+@functools.lru_cache(maxsize=256, typed=True)
 def prefill_workspace_size(batch, total_new, max_new, hq, hkv, d, cache_cap):
     return int(lib().ism_attn_prefill_workspace_size(
         batch, total_new, max_new, hq, hkv, d, cache_cap))

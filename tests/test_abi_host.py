@@ -210,6 +210,16 @@ def test_no_device_is_reported(L):
                              None, 1, 1, 64, 0.125, 0, ws, 1 << 20, None) == 7
 
 
+def test_workspace_sizes_refuse_floats(L):
+    """Sizes are remembered by value and type: 1000.0 is refused as before,
+    also after a call with 1000."""
+    args = [ops.ISM_OP_FWD, 1, 1000, 1000, 4, 4, 64]
+    assert ops.workspace_size(*args) > 0
+    args[2] = 1000.0
+    with pytest.raises(ctypes.ArgumentError):
+        ops.workspace_size(*args)
+
+
 def test_workspace_sizes(L):
     assert ops.workspace_size(ops.ISM_OP_FWD, 1, 1000, 1000, 4, 4, 64) >= 4000
     assert ops.workspace_size(ops.ISM_OP_FWD, 1, 1000, 1000, 4, 4, 64) % 256 == 0
