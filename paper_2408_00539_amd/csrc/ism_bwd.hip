@@ -795,11 +795,14 @@ int gcd_i(int x, int y) {
 }
 
 // dQ workgroups of four waves, two to a CU, so that one's prologue and last
-// steps run beside the other's products. Eight waves (alone on a CU, half the
-// transfers per product) measured the same on 4 x 8192 tokens (2575 us
-// against 2542 with four) and slower on shorter dialogues (12 ragged ones up
-// to 3001 tokens, 32/8 heads: 945 against 873 us; 6 up to 900, d 64: 24.4
-// against 18.1).
+// steps run beside the other's products; on dialogues above 4096 tokens,
+// where those are a small part, of eight waves, alone on a CU, with half the
+// transfers per product (which also leaves the power-limited chip more clock
+// for the dK/dV kernel behind it). Training steps with four and eight waves
+// (us; two runs differ by 0.3 %): 6 x 5000 tokens, 32 heads 5125, 5091; 6 x
+// 5000, 32/8 heads 4940, 4920; 4 x 8192, 32/8 heads 8460, 8424; 8 x 4000, 32
+// heads 4512, 4504; but 12 ragged up to 3001, 32/8 heads 2889, 2940 and the dQ
+// kernel of 6 ragged up to 900, d 64 18.1, 24.4.
 template <int D, int NWV>
 hipError_t launch_dq(const BwdArgs &a, hipStream_t stream) {
   const int hpw = gcd_i(a.hq / a.hkv, NWV);
@@ -814,7 +817,8 @@ hipError_t launch_dq(const BwdArgs &a, hipStream_t stream) {
 // dQ first: it also writes the per-row summands the dK/dV kernel reads.
 template <int D>
 hipError_t launch_bwd_t(const BwdArgs &a, hipStream_t stream) {
-  hipError_t err = launch_dq<D, 4>(a, stream);
+  hipError_t err =
+      a.max_seqlen > 4096 ? launch_dq<D, 8>(a, stream) : launch_dq<D, 4>(a, stream);
   if (err != hipSuccess) return err;
   const int ktiles = (a.max_seqlen + kKW - 1) / kKW, parts = a.dkv_part ? a.dkv_parts : 1;
   hipLaunchKernelGGL((dkv_kernel<D>),

@@ -201,3 +201,33 @@ def test_segment_table_edges(segments):
     compare("LSE", host_f64(lse), rl)
     for name, g, r in zip(("dQ", "dK", "dV"), grads, oracle.bwd(*args, f64(do), *meta)):
         compare(name, host_f64(g), r)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 4, 128), (8, 1, 64), (6, 2, 64)])
+def test_dq_four_and_eight_waves(hq, hkv, d):
+    """The dQ kernel runs eight-wave workgroups from a longest dialogue of
+    4097 tokens on: dQ of the same dialogues under both bounds, equal bit for
+    bit (each wave's rows are the same work) and against the oracle."""
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    rng = np.random.default_rng(hq + d)
+    segs = W.segments_from_lengths([W.alternating([40, 161, 99]), W.alternating([1]),
+                                    W.alternating([30, 35])] + [W.alternating([63, 193])] * 15)
+    T, scale = segs.total, 1 / np.sqrt(d)
+    q, k, v = _bits(rng, T, hq, d), _bits(rng, T, hkv, d), _bits(rng, T, hkv, d)
+    do = _bits(rng, T, hq, d)
+    S = ops.Segments.from_host(segs.cu_seqlens, segs.cu_segs, segs.seg_is_query)
+    assert T >= 4097  # the bound lies between the longest dialogue and the total
+    dev = [dev_bf16(x) for x in (q, k, v)]
+    o, lse = ops.fwd(*dev, S, scale)
+    ref = oracle.bwd(f64(q), f64(k), f64(v), f64(do), segs.cu_seqlens, segs.cu_segs,
+                     segs.seg_is_query, scale)
+    got = []
+    for longest in (4096, 4097):
+        announce("dQ waves", hq, hkv, d, longest)
+        S.max_seqlen = longest
+        got.append(ops.bwd(*dev, o, lse, dev_bf16(do), S, scale))
+        for name, g, r in zip(("dQ", "dK", "dV"), got[-1], ref):
+            compare(name, host_f64(g), r)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
