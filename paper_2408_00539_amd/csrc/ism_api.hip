@@ -13,14 +13,17 @@
 #include "ism_common.h"
 #include "ism_host.h"
 #include "ism_kernels.h"
+#include "ism_split_plan.h"
 
 namespace {
 
+using ism::align_up;
 using ism::fail;
-
-constexpr size_t kAlign = 256;
-
-size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+using ism::kAlign;
+using ism::PrefillKind;
+using ism::prefill_kind;
+using ism::split_plan;
+using ism::SplitPlan;
 
 // Device check, cached per device ordinal: a gfx950 device must be current.
 ism_status check_device() {
@@ -173,77 +176,6 @@ size_t decode_min_workspace(int32_t batch, int32_t max_len, int32_t hq, int32_t 
   return align_up((size_t)batch * hq * s * d * 4) + align_up((size_t)batch * hq * s * 2 * 4);
 }
 
-// The host part of a split-key launch: the columns of a workgroup and how
-// many units to make. One-wave workgroups of 32 columns and 32-key tiles
-// (ism_split.hip, where the unit counts are measured), or the forward
-// kernel's of 128 columns and 64-key tiles. At least 128 or 256 keys per
-// chunk, at most 64 chunks.
-struct SplitPlan {
-  int32_t colw, col_groups, col_stride, budget, max_units, max_splits, tile_shift, min_tiles;
-  // workspace of the partials and the plan (0: one chunk per dialogue)
-  size_t part_bytes, ml_bytes, plan_bytes;
-  size_t bytes() const { return part_bytes + ml_bytes + plan_bytes; }
-};
-
-constexpr int kSplitUnits = 640, kSplitUnits64 = 960, kSplitUnits128 = 448;
-// From this many (dialogue, KV head, column group) workgroups on (1280 one-wave
-// workgroups fit the chip), a one-wave launch keeps every dialogue whole and
-// needs no plan, whose scans over many dialogues every workgroup would repeat.
-// Measured with the plan and without (us): decode, 32/8 heads, 256 ragged
-// dialogues up to 1000 keys 106.3, 101.6; 1000: 404, 347; 2000: 1080, 845; 8
-// drafted rows over 300 ragged up to 800 keys 128, 114; 64/8 heads, d 64, 256
-// x 300 keys 34.9, 28.1. Below it, splitting the long dialogues of a ragged
-// batch is worth the plan.
-constexpr int kSplitDirect = 2048;
-SplitPlan split_plan(int32_t batch, int64_t total_rows, int32_t max_rows, int32_t hq, int32_t hkv,
-                     int32_t d, int64_t max_len, int32_t fixed, bool limited, size_t ws_bytes) {
-  SplitPlan p{};
-  const int64_t cols = (int64_t)max_rows * (hq / hkv);
-  const bool one_wave = cols <= 32 || max_rows == 1;
-  p.colw = one_wave ? 32 : 128;
-  p.tile_shift = one_wave ? 5 : 6;
-  p.min_tiles = 4;
-  p.col_groups = (int32_t)((cols + p.colw - 1) / p.colw);
-  p.col_stride = (int32_t)(cols < p.colw ? cols : p.colw);
-  const int target = !one_wave ? kSplitUnits128 : d == 64 ? kSplitUnits64 : kSplitUnits;
-  p.budget = (target + hkv - 1) / hkv;
-  const int64_t tiles = (max_len + (1 << p.tile_shift) - 1) >> p.tile_shift;
-  const int64_t most = fixed > 0 ? fixed : (tiles + p.min_tiles - 1) / p.min_tiles;
-  p.max_splits = (int32_t)(most < 1 ? 1 : fixed <= 0 && most > 64 ? 64 : most);
-  if (one_wave && fixed <= 0 && (int64_t)batch * hkv * p.col_groups >= kSplitDirect)
-    p.max_splits = 1;
-  // column groups of all dialogues together, partials of one unit over all
-  // KV heads
-  const int64_t by_rows = total_rows * (hq / hkv) / p.colw + batch, groups = p.col_groups;
-  const int64_t all_groups = by_rows < (int64_t)batch * groups ? by_rows : (int64_t)batch * groups;
-  const int64_t per = (int64_t)hkv * p.col_stride * (d + 2) * 4;
-  int64_t units = all_groups * p.max_splits;
-  if (fixed <= 0 && units > (int64_t)p.budget + all_groups) units = (int64_t)p.budget + all_groups;
-  const int64_t rest = (int64_t)align_up((size_t)batch * 2 * 4) + 2 * (int64_t)kAlign;
-  if (limited && p.max_splits > 1 && units * per + rest > (int64_t)ws_bytes) {
-    // a smaller workspace: fewer units, down to one chunk per dialogue
-    const int64_t fit = ((int64_t)ws_bytes - rest) / per;
-    if (fixed > 0 && fit >= all_groups) {
-      p.max_splits = (int32_t)(fit / all_groups);
-      units = all_groups * p.max_splits;
-    } else if (fixed <= 0 && fit > all_groups) {
-      p.budget = (int32_t)(fit - all_groups);
-      units = fit;
-    } else {
-      p.max_splits = 1;
-    }
-  }
-  if (p.max_splits == 1) {
-    p.max_units = (int32_t)all_groups;
-    return p;
-  }
-  p.max_units = (int32_t)units;
-  p.part_bytes = align_up((size_t)units * hkv * p.col_stride * d * 4);
-  p.ml_bytes = align_up((size_t)units * hkv * p.col_stride * 2 * 4);
-  p.plan_bytes = align_up((size_t)batch * 2 * 4);
-  return p;
-}
-
 void apply_plan(ism::SplitArgs &a, const SplitPlan &p, int32_t fixed, void *ws) {
   a.colw = p.colw; a.col_groups = p.col_groups; a.col_stride = p.col_stride;
   a.budget = p.budget; a.inv_budget = 1.0001f / (float)p.budget;
@@ -252,26 +184,6 @@ void apply_plan(ism::SplitArgs &a, const SplitPlan &p, int32_t fixed, void *ws) 
   a.part_o = (float *)ws;
   a.part_ml = (float *)((char *)ws + p.part_bytes);
   a.plan = p.max_splits > 1 ? (int32_t *)((char *)ws + p.part_bytes + p.ml_bytes) : nullptr;
-}
-
-// How a cached prefill runs: kOneWave when the (row, query head) pairs of the
-// longest new segment that share a KV head fill at most one 32-column block,
-// so that the cache is streamed once (two blocks would stream it twice: the
-// row-tiled forward kernel shares its K/V tiles among four waves); else the
-// forward kernel, its key ranges split into about 448 units when its
-// workgroups leave most of the 512 that fit the chip unused. Measured
-// unsplit against split (us), by workgroups: 32 (8 ragged dialogues up to
-// 12000 keys, 16 rows, 32/2 heads) 172, 43; 32 (1 x 4000, 100 rows, 32/8) 64,
-// 31; 160 (10 x 3000, 50 rows, 32/8) 61, 55; 236 (8 ragged up to 3000, 200
-// rows, 32/2) 83, 114; 320 (20 ragged up to 4000, 60 rows, 32/8) 95, 120: the
-// partials of that many rows cost more than the idle workgroups.
-enum PrefillKind { kRowTiles, kRowTilesSplit, kOneWave };
-PrefillKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_new, int32_t hq,
-                         int32_t hkv) {
-  const int64_t g = hq / hkv;
-  if (max_new * g <= 32) return kOneWave;
-  const int64_t wgs = hkv * (total_new * g / 128 + batch);
-  return wgs < 192 ? kRowTilesSplit : kRowTiles;
 }
 
 // Short calls, whose kernels form the Eq. 5 bounds from the segments in LDS:
@@ -314,7 +226,8 @@ extern "C" size_t ism_attn_workspace_size(int32_t op, int32_t batch,
     case ISM_OP_DECODE: {
       if (hkv < 1 || hq < hkv || hq % hkv) return 0;
       if (!ism::decode_vector(batch, hq, hkv)) {
-        const SplitPlan p = split_plan(batch, batch, 1, hq, hkv, d, max_seqlen, num_splits, false, 0);
+        const SplitPlan p = split_plan(ism::kOneWave, batch, batch, 1, hq, hkv, d, max_seqlen,
+                                       num_splits, false, 0);
         const size_t need = decode_min_workspace(batch, max_seqlen, hq, hkv, d, num_splits);
         return need > p.bytes() ? need : p.bytes();
       }
@@ -327,11 +240,13 @@ extern "C" size_t ism_attn_workspace_size(int32_t op, int32_t batch,
 extern "C" size_t ism_attn_prefill_workspace_size(int32_t batch, int32_t total_new,
                                                   int32_t max_new, int32_t hq, int32_t hkv,
                                                   int32_t d, int32_t cache_cap) {
-  if (batch < 1 || total_new < 1 || max_new < 1 || hkv < 1 || hq < hkv || hq % hkv || d < 1 || cache_cap < 1 ||
-      prefill_kind(batch, total_new, max_new, hq, hkv) == kRowTiles)
+  if (batch < 1 || total_new < 1 || max_new < 1 || hkv < 1 || hq < hkv || hq % hkv || d < 1 ||
+      cache_cap < 1)
     return 0;
-  const SplitPlan p = split_plan(batch, total_new, max_new, hq, hkv, d, cache_cap, 0, false, 0);
-  return p.bytes();
+  const PrefillKind kind = prefill_kind(batch, total_new, max_new, hq, hkv);
+  return kind == ism::kRowTiles ? 0
+                                : split_plan(kind, batch, total_new, max_new, hq, hkv, d,
+                                             cache_cap, 0, false, 0).bytes();
 }
 
 extern "C" ism_status ism_attn_fwd(const ism_segments *sg, const void *q,
@@ -511,7 +426,7 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
   const PrefillKind kind =
       split_need == 0 || (ws && (uintptr_t)ws % kAlign == 0 && ws_bytes >= split_need)
           ? prefill_kind(batch, total_new, max_new, hq, hkv)
-          : kRowTiles;
+          : ism::kRowTiles;
   if ((st = check_device())) return st;
   if ((st = validate_new_lengths(cu_seqlens_new, batch, total_new, max_new,
                                  (hipStream_t)stream)))
@@ -524,7 +439,7 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
     ae = ism::launch_cache_append_rope(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
                                        cache_seqlens, rp->pos1, rp->pos2, l2b, batch, max_new,
                                        hkv, d, cache_cap, s);
-  else if (kind == kOneWave)
+  else if (kind == ism::kOneWave)
     ;  // its kernel appends
   else if (pg)
     ae = ism::launch_cache_append_paged(k_new, v_new, k_cache, v_cache, cu_seqlens_new,
@@ -535,7 +450,7 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
                                   batch, max_new, hkv, d, cache_cap, s);
   if ((st = hip_status(ae, "cache append launch"))) return st;
   ism::SplitArgs sp{};
-  if (kind != kRowTiles) {
+  if (kind != ism::kRowTiles) {
     ism::SplitArgs &a = sp;
     a.q = q_new; a.k_new = k_new; a.v_new = v_new; a.k_cache = k_cache; a.v_cache = v_cache;
     a.cu_new = cu_seqlens_new; a.cache_len = cache_seqlens; a.o = o; a.lse = lse;
@@ -544,7 +459,8 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
     a.scale = scale;
     a.causal = seg_is_query ? 0 : 1;
     a.append = rp ? 0 : 1;
-    apply_plan(a, split_plan(batch, total_new, max_new, hq, hkv, d, cache_cap, 0, false, 0), 0, ws);
+    apply_plan(a, split_plan(kind, batch, total_new, max_new, hq, hkv, d, cache_cap, 0, false, 0),
+               0, ws);
     if (pg) {
       a.block_table = pg->block_table;
       a.max_pages = pg->max_pages;
@@ -556,7 +472,7 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
       a.rope_pos2 = rp->pos2;
       a.rope_log2_base = l2b;
     }
-    if (kind == kOneWave)
+    if (kind == ism::kOneWave)
       return hip_status(ism::launch_split(a, d, s), "cached prefill launch");
   }
   ism::FwdArgs a{};
@@ -583,7 +499,7 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
     a.rope_pos2 = rp->pos2;
     a.rope_log2_base = l2b;
   }
-  return hip_status(kind == kRowTilesSplit ? ism::launch_fwd_split(a, sp, d, s)
+  return hip_status(kind == ism::kRowTilesSplit ? ism::launch_fwd_split(a, sp, d, s)
                                            : ism::launch_fwd(a, d, true, s),
                     "cached prefill launch");
 }
@@ -696,8 +612,8 @@ ism_status decode_impl(const void *q, const void *k_new, const void *v_new, void
     a.total_q = batch; a.max_rows = 1;
     a.scale = scale;
     a.append = 1;
-    apply_plan(a, split_plan(batch, batch, 1, hq, hkv, d, max_seqlen, num_splits, true, ws_bytes),
-               num_splits, ws);
+    apply_plan(a, split_plan(ism::kOneWave, batch, batch, 1, hq, hkv, d, max_seqlen, num_splits,
+                             true, ws_bytes), num_splits, ws);
     if (pg) {
       a.block_table = pg->block_table;
       a.max_pages = pg->max_pages;

@@ -628,6 +628,7 @@ hipError_t launch_fwd_split_p(const FwdArgs &a, const SplitArgs &sp, hipStream_t
 }  // namespace
 
 hipError_t launch_fwd_split(const FwdArgs &a, const SplitArgs &sp, int d, hipStream_t stream) {
+  if (sp.colw != 4 * kQW || 1 << sp.tile_shift != kBN) return hipErrorInvalidValue;
   if (d == 128) return a.block_table ? launch_fwd_split_p<128, true>(a, sp, stream)
                                      : launch_fwd_split_p<128, false>(a, sp, stream);
   if (d == 64) return a.block_table ? launch_fwd_split_p<64, true>(a, sp, stream)

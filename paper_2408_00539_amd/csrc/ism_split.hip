@@ -367,6 +367,7 @@ hipError_t launch_split_combine(const SplitArgs &a, int d, hipStream_t stream) {
 }
 
 hipError_t launch_split(const SplitArgs &a, int d, hipStream_t stream) {
+  if (a.colw != 32 || 1 << a.tile_shift != kT) return hipErrorInvalidValue;
   if (d == 128) return a.block_table ? launch_split_p<128, true>(a, stream)
                                      : launch_split_p<128, false>(a, stream);
   if (d == 64) return a.block_table ? launch_split_p<64, true>(a, stream)

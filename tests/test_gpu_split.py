@@ -42,6 +42,12 @@ def _hist(rng, batch, longest):
     (5, 1300, 2, 2, 64, 200, False),
     (11, 900, 16, 1, 64, 40, True),
     (3, 5000, 3, 1, 128, 33, False),
+    # one new row whose heads alone fill more than one 32-column block
+    (5, 4000, 40, 1, 64, 1, True),
+    (4, 8000, 64, 1, 128, 1, False),
+    (3, 4100, 160, 1, 64, 1, False),
+    (11, 900, 256, 1, 128, 1, True),
+    (5, 1300, 512, 2, 128, 1, False),
 ])
 def test_ragged_chunks(batch, longest, hq, hkv, d, new, is_query):
     torch = torch_cuda()

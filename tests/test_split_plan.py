@@ -1,0 +1,127 @@
+"""The split-key plan on the host: csrc/ism_split_plan.h (built here as plain
+C++) with the device side of csrc/ism_plan.h repeated in numpy, so that every
+read and write that the plan leads to is checked without a GPU.
+
+The kernels' own shapes are the reference: split_attn_kernel serves 32
+columns and steps 32 keys, the forward kernel 128 columns and 64 keys.
+"""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2408_00539_amd", "csrc")
+SHIM = """
+#include "ism_split_plan.h"
+extern "C" int kind_of(int batch, long total, int rows, int hq, int hkv) {
+  return ism::prefill_kind(batch, total, rows, hq, hkv);
+}
+extern "C" void plan_of(int kind, int batch, long total, int rows, int hq, int hkv, int d,
+                        long max_len, int fixed, int limited, long ws, long *out) {
+  const ism::SplitPlan p = ism::split_plan((ism::PrefillKind)kind, batch, total, rows, hq, hkv, d,
+                                           max_len, fixed, limited, ws);
+  const long v[] = {p.colw, p.col_groups, p.col_stride, p.budget, p.max_units, p.max_splits,
+                    p.tile_shift, p.min_tiles, (long)p.part_bytes, (long)p.ml_bytes,
+                    (long)p.plan_bytes};
+  for (int i = 0; i < 11; ++i) out[i] = v[i];
+}
+"""
+ROW_TILES, ROW_TILES_SPLIT, ONE_WAVE = 0, 1, 2
+COLS = {ROW_TILES_SPLIT: 128, ONE_WAVE: 32}
+KEYS = {ROW_TILES_SPLIT: 64, ONE_WAVE: 32}
+
+
+class Plan:
+    def __init__(self, lib, kind, batch, total, rows, hq, hkv, d, max_len, fixed=0, ws=None):
+        out = (ctypes.c_long * 11)()
+        lib.plan_of(kind, batch, ctypes.c_long(total), rows, hq, hkv, d, ctypes.c_long(max_len),
+                    fixed, ws is not None, ctypes.c_long(ws or 0), out)
+        (self.colw, self.col_groups, self.col_stride, self.budget, self.max_units,
+         self.max_splits, self.tile_shift, self.min_tiles, self.part_bytes, self.ml_bytes,
+         self.plan_bytes) = out
+        self.key = tuple(out)
+        self.bytes = self.part_bytes + self.ml_bytes + self.plan_bytes
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    cxx = shutil.which(os.environ.get("CXX", "g++"))
+    if not cxx:
+        pytest.skip("no host compiler")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cpp").write_text(SHIM)
+    r = subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                        "-I" + CSRC, "-o", str(d / "shim.so"), str(d / "shim.cpp")],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    out = ctypes.CDLL(str(d / "shim.so"))
+    out.kind_of.argtypes = [ctypes.c_int, ctypes.c_long] + 3 * [ctypes.c_int]
+    return out
+
+
+def units(p, cached, rows, group, cap, fixed=0):
+    """(dialogue, chunk, chunks, first tile, tiles, keys, column groups) of
+    every unit of one KV head, as the device plan makes them."""
+    keys = np.clip(cached.astype(np.int64) + rows, 1, cap)
+    t = np.where(rows > 0, ((keys - 1) >> p.tile_shift) + 1, 0)
+    g = np.minimum(-(-rows.astype(np.int64) * group // p.colw), p.col_groups)
+    lc = 1
+    if not fixed and p.max_splits > 1:
+        s = np.float32((t * g).sum())
+        per = s * (np.float32(1.0001) / np.float32(p.budget))
+        lc = max(int(per) + 1, p.min_tiles)
+    out = []
+    for b in range(len(rows)):
+        n = min(fixed or -(-int(t[b]) // lc), p.max_splits)
+        per = max(int(t[b]), 1) if n <= 1 else -(-int(t[b]) // n)
+        n = -(-int(t[b]) // per)
+        out += [(b, i, n, i * per, min(per, int(t[b]) - i * per), int(keys[b]), int(g[b]))
+                for i in range(n)]
+    return out
+
+
+def check(p, kind, cached, rows, hq, hkv, d, cap, fixed=0):
+    group = hq // hkv
+    assert (p.colw, 1 << p.tile_shift) == (COLS[kind], KEYS[kind])
+    u = units(p, cached, rows, group, cap, fixed)
+    # the grid, and the partials that it writes
+    assert sum(x[-1] for x in u) <= p.max_units
+    if p.max_splits > 1:
+        slots = p.max_units * hkv * p.col_stride
+        assert p.part_bytes >= slots * d * 4 and p.ml_bytes >= slots * 8
+        assert p.plan_bytes >= len(rows) * 8
+    for b, i, n, tile0, tiles, keys, g in u:
+        # every chunk begins at a key that exists, and the last one ends at the end
+        assert tiles > 0 and tile0 * KEYS[kind] < keys <= cap
+        assert (i == n - 1) == ((tile0 + tiles) * KEYS[kind] >= keys)
+        # the columns of a group fit its slot, and the groups hold every column
+        cols = int(rows[b]) * group
+        assert g * COLS[kind] >= cols and min(cols, COLS[kind]) <= p.col_stride
+
+
+HEADS = (1, 2, 3, 8, 31, 32, 33, 40, 64, 127, 128, 129, 160, 256, 320, 4096)
+
+
+@pytest.mark.parametrize("rows", [1, 2, 3, 8, 32, 33, 100])
+def test_prefill_plan_fits_its_kernel(lib, rows):
+    """Over new rows and query heads per KV head, dense and ragged."""
+    rng = np.random.default_rng(rows)
+    kinds = set()
+    for group in HEADS:
+        for hkv, batch in ((1, 1), (1, 3), (2, 11), (8, 70), (4, 600)):
+            kind = lib.kind_of(batch, rows * batch, rows, hkv * group, hkv)
+            if kind == ROW_TILES:
+                continue
+            kinds.add(kind)
+            for cap in (rows + 63, 4096, 8192, 200000):
+                p = Plan(lib, kind, batch, rows * batch, rows, hkv * group, hkv, 128, cap)
+                for cached in (np.full(batch, cap - rows), np.full(batch, max(0, cap // 2 - rows)),
+                               rng.integers(0, cap - rows + 1, size=batch)):
+                    for new in (np.full(batch, rows), rng.integers(0, rows + 1, size=batch)):
+                        check(p, kind, cached, new, hkv * group, hkv, 128, cap)
+    assert ROW_TILES_SPLIT in kinds and (rows > 32 or ONE_WAVE in kinds)
