@@ -79,28 +79,31 @@ inline SplitPlan split_plan(PrefillKind kind, int32_t batch, int64_t total_rows,
   const int64_t per = (int64_t)hkv * p.col_stride * (d + 2) * 4;
   int64_t units = all_groups * p.max_splits;
   if (fixed <= 0 && units > (int64_t)p.budget + all_groups) units = (int64_t)p.budget + all_groups;
-  const int64_t rest = (int64_t)align_up((size_t)batch * 2 * 4) + 2 * (int64_t)kAlign;
-  if (limited && p.max_splits > 1 && units * per + rest > (int64_t)ws_bytes) {
-    // a smaller workspace: fewer units, down to one chunk per dialogue
-    const int64_t fit = ((int64_t)ws_bytes - rest) / per;
+  auto layout = [&](int64_t n) {
+    p.max_units = (int32_t)n;
+    p.part_bytes = align_up((size_t)n * hkv * p.col_stride * d * 4);
+    p.ml_bytes = align_up((size_t)n * hkv * p.col_stride * 2 * 4);
+    p.plan_bytes = align_up((size_t)batch * 2 * 4);
+  };
+  layout(units);
+  if (limited && p.max_splits > 1 && p.bytes() > ws_bytes) {
+    // a smaller workspace: fewer units, down to one chunk per dialogue (the
+    // two partial buffers are rounded up, by less than kAlign each)
+    const int64_t fit = ((int64_t)ws_bytes - (int64_t)p.plan_bytes - 2 * (int64_t)kAlign) / per;
     if (fixed > 0 && fit >= all_groups) {
       p.max_splits = (int32_t)(fit / all_groups);
-      units = all_groups * p.max_splits;
+      layout(all_groups * p.max_splits);
     } else if (fixed <= 0 && fit > all_groups) {
       p.budget = (int32_t)(fit - all_groups);
-      units = fit;
+      layout(fit);
     } else {
       p.max_splits = 1;
     }
   }
   if (p.max_splits == 1) {
     p.max_units = (int32_t)all_groups;
-    return p;
+    p.part_bytes = p.ml_bytes = p.plan_bytes = 0;
   }
-  p.max_units = (int32_t)units;
-  p.part_bytes = align_up((size_t)units * hkv * p.col_stride * d * 4);
-  p.ml_bytes = align_up((size_t)units * hkv * p.col_stride * 2 * 4);
-  p.plan_bytes = align_up((size_t)batch * 2 * 4);
   return p;
 }
 

@@ -125,3 +125,27 @@ def test_prefill_plan_fits_its_kernel(lib, rows):
                     for new in (np.full(batch, rows), rng.integers(0, rows + 1, size=batch)):
                         check(p, kind, cached, new, hkv * group, hkv, 128, cap)
     assert ROW_TILES_SPLIT in kinds and (rows > 32 or ONE_WAVE in kinds)
+
+
+DECODES = [(1, 32, 8, 128, 2500), (1, 32, 8, 128, 8192), (9, 8, 2, 128, 3000),
+           (9, 40, 1, 64, 3000), (4, 32, 8, 128, 3000), (40, 32, 8, 128, 4000),
+           (30, 16, 8, 64, 5000), (3, 64, 1, 128, 130), (200, 64, 8, 128, 900)]
+
+
+@pytest.mark.parametrize("batch,hq,hkv,d,max_len", DECODES)
+@pytest.mark.parametrize("fixed", [0, 1, 2, 3, 16, 64])
+def test_decode_plan_in_its_workspace(lib, batch, hq, hkv, d, max_len, fixed):
+    """With a workspace of the plan's own size it is the plan without a limit;
+    smaller ones give plans that fit them."""
+    rng = np.random.default_rng(batch + fixed)
+    args = (lib, ONE_WAVE, batch, batch, 1, hq, hkv, d, max_len, fixed)
+    full = Plan(*args)
+    assert Plan(*args, ws=full.bytes).key == full.key
+    rows = np.ones(batch, dtype=np.int64)
+    for ws in [full.bytes * i // 16 // 256 * 256 for i in range(1, 16)] + [256, full.bytes - 256]:
+        if ws <= 0:
+            continue
+        p = Plan(*args, ws=ws)
+        assert p.bytes <= ws and p.max_units <= full.max_units
+        for cached in (np.full(batch, max_len - 1), rng.integers(0, max_len, size=batch)):
+            check(p, ONE_WAVE, cached, rows, hq, hkv, d, max_len, fixed)

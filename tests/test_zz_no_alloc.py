@@ -45,6 +45,29 @@ def test_noalloc_matches_decode_twice(hq, hkv, d):
         assert torch.equal(vc2.view(torch.int16), vc.view(torch.int16))
 
 
+@pytest.mark.parametrize("lens,hq,hkv,d,splits", [
+    ([2500], 32, 8, 128, 0),          # one dialogue: as many chunks as its keys allow
+    ([8191], 32, 8, 128, 0),
+    ([2999] * 9, 8, 2, 128, 0),
+    ([2999, 17, 1500], 8, 2, 64, 2),  # asked-for chunk counts
+    ([2999, 17, 1500], 8, 2, 64, 64),
+])
+def test_noalloc_cuts_the_same_chunks(lens, hq, hkv, d, splits):
+    """The step with a workspace of its own (ops.decode) and with the larger
+    scratch cut the keys alike: the same bits."""
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    rng = np.random.default_rng(sum(lens) + splits)
+    cap = max(lens) + 1
+    announce("decode_noalloc chunks", lens, hq, hkv, d, splits)
+    q, kn, vn, kc, vc, pos = _case(rng, len(lens), hq, hkv, d, cap, lens)
+    o_ref, l_ref = ops.decode(q, kn, vn, kc.clone(), vc.clone(), pos, num_splits=splits)
+    o, l = torch.full_like(o_ref, float("nan")), torch.full_like(l_ref, float("nan"))
+    ops.decode_noalloc(q, kn, vn, kc, vc, pos, num_splits=splits, out=(o, l))
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), o_ref.view(torch.int16)) and torch.equal(l, l_ref)
+
+
 def test_noalloc_rejects_partials_beyond_scratch():
     """64 dialogues x 64 heads x 64 splits x (128 + 2) x 4 bytes is far above
     the scratch: refused before any launch, outputs untouched."""
