@@ -213,16 +213,16 @@ ism_status ism_attn_decode(const void *q, const void *k_new, const void *v_new,
 /* The decode step of ism_attn_decode for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation): the same arguments without the
- * workspace. The split partials live in a fixed per-device scratch array of
- * ISM_NOALLOC_SCRATCH_BYTES that the library holds until the process ends
- * (its device address is looked up on the first call on each device); the
- * call allocates nothing. Calls whose partials need more (batch * hq *
- * splits * (d + 2) * 4 bytes, rounded up) fail with ISM_ERR_WORKSPACE
- * before any launch. Every call on a device shares that device's scratch:
+ * workspace. The split partials live in a fixed per-device scratch array
+ * (32 MiB) that the library holds until the process ends (its device address
+ * is looked up on the first call on each device); the call allocates
+ * nothing. Calls whose smallest workspace (ism_attn_decode) is above
+ * ISM_NOALLOC_SCRATCH_BYTES fail with ISM_ERR_WORKSPACE before any launch.
+ * Every call on a device shares that device's scratch:
  * calls that may overlap on one device (different streams, no ordering
  * between them) race and must be serialised by the caller. Results equal
- * those of ism_attn_decode given a workspace of the same size bit for bit
- * (and given a larger one, unless that cuts more chunks). */
+ * those of ism_attn_decode with the workspace that ism_attn_workspace_size
+ * gives, bit for bit. */
 #define ISM_NOALLOC_SCRATCH_BYTES (8u << 20)
 ism_status ism_attn_decode_noalloc(const void *q, const void *k_new,
                                    const void *v_new, void *k_cache,

@@ -679,7 +679,15 @@ namespace {
 // until the process ends. Host code never passes this name to a kernel (on
 // the host it is only a stand-in for the device symbol): it uses the device
 // address that hipGetSymbolAddress returns for the current device.
-static __device__ __align__(256) unsigned char scratch[ISM_NOALLOC_SCRATCH_BYTES];
+// It holds the whole plan of every step that is accepted (whose smallest
+// workspace is at most ISM_NOALLOC_SCRATCH_BYTES), so that the step cuts the
+// keys as ism_attn_decode does with its recommended workspace: the plan's
+// partials are those of at most 640 (d = 128) or 960 chunks of 32 columns,
+// hq more, and 2 batch hq (column groups of 32 more than fill half), of
+// (d + 2) * 4 bytes each, where batch hq (d + 2) * 4 is at most that limit and
+// hq at most 8192: 31.9e6 bytes.
+constexpr size_t kScratchBytes = 32u << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[64];  // per device ordinal, set on the first call there
@@ -727,13 +735,12 @@ extern "C" ism_status ism_attn_decode_noalloc(const void *q, const void *k_new,
   const size_t need = decode_min_workspace(batch, ms, hq, hkv, d, num_splits);
   if (need > ISM_NOALLOC_SCRATCH_BYTES)
     return fail(ISM_ERR_WORKSPACE,
-                "split partials need %zu bytes, above the %zu-byte scratch of the "
+                "split partials need %zu bytes, above the %zu-byte limit of the "
                 "allocation-free decode (use ism_attn_decode with a workspace)",
                 need, (size_t)ISM_NOALLOC_SCRATCH_BYTES);
   if ((st = check_device())) return st;
   void *ws = nullptr;
   if ((st = scratch_address(&ws))) return st;
   return decode_impl(q, k_new, v_new, k_cache, v_cache, cache_cap, cache_seqlens, batch, ms, o,
-                     lse, hq, hkv, d, scale, num_splits, ws, ISM_NOALLOC_SCRATCH_BYTES, stream,
-                     nullptr);
+                     lse, hq, hkv, d, scale, num_splits, ws, kScratchBytes, stream, nullptr);
 }

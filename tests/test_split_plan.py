@@ -8,6 +8,7 @@ columns and steps 32 keys, the forward kernel 128 columns and 64 keys.
 
 import ctypes
 import os
+import re
 import shutil
 import subprocess
 
@@ -149,3 +150,28 @@ def test_decode_plan_in_its_workspace(lib, batch, hq, hkv, d, max_len, fixed):
         assert p.bytes <= ws and p.max_units <= full.max_units
         for cached in (np.full(batch, max_len - 1), rng.integers(0, max_len, size=batch)):
             check(p, ONE_WAVE, cached, rows, hq, hkv, d, max_len, fixed)
+
+
+def test_accepted_noalloc_steps_fit_the_scratch(lib):
+    """Every step whose smallest workspace is at most the limit of
+    ism_attn_decode_noalloc fits its whole plan into the library's scratch."""
+    text = open(os.path.join(CSRC, "ism_api.hip")).read()
+    scratch = int(re.search(r"kScratchBytes = (\d+)u << 20", text).group(1)) << 20
+    limit, most = 8 << 20, 0
+    for d in (64, 128):
+        for group in HEADS:
+            for hkv in (1, 2, 8, 32, 100, 256):
+                hq = group * hkv
+                if hq > 8192:
+                    continue
+                top = limit // (hq * (d + 2) * 4)
+                for batch in {1, 2, 3, 17, top // 3, top}:
+                    for fixed in (0, 1, 2, 64):
+                        # the smallest workspace holds at least this
+                        if batch < 1 or batch * hq * max(fixed, 1) * (d + 2) * 4 > limit:
+                            continue
+                        for max_len in (1, 700, 8192, 1 << 20):
+                            p = Plan(lib, ONE_WAVE, batch, batch, 1, hq, hkv, d, max_len, fixed)
+                            most = max(most, p.bytes)
+                            assert p.bytes <= scratch, (batch, hq, hkv, d, fixed, max_len)
+    assert most > limit

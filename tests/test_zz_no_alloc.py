@@ -51,6 +51,7 @@ def test_noalloc_matches_decode_twice(hq, hkv, d):
     ([2999] * 9, 8, 2, 128, 0),
     ([2999, 17, 1500], 8, 2, 64, 2),  # asked-for chunk counts
     ([2999, 17, 1500], 8, 2, 64, 64),
+    ([6000] * 8, 64, 2, 128, 0),      # the plan's partials fill 10.9e6 bytes
 ])
 def test_noalloc_cuts_the_same_chunks(lens, hq, hkv, d, splits):
     """The step with a workspace of its own (ops.decode) and with the larger
