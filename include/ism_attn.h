@@ -198,10 +198,14 @@ ism_status ism_attn_prefill_cached_segment(
  * replaced by cache_cap), hq, hkv, d, num_splits). Any hq / hkv is
  * supported: with 4 or more query heads per KV head, or on a step of fewer
  * than 512 (dialogue, KV head) pairs, the step runs on the matrix cores,
- * otherwise on the vector ALU. That size leaves room for about 640 chunks
- * of all dialogues together; a smaller workspace, down to batch * hq *
- * splits * (d + 2) * 4 bytes (rounded up) with one chunk per 256 keys, at
- * most 64, or num_splits, is accepted and cuts fewer. */
+ * otherwise on the vector ALU. On the matrix cores the automatic plan cuts
+ * the dialogues' keys into chunks of about one length for the whole batch, at
+ * most 1024 over all KV heads and groups of 32 heads while whole dialogues
+ * are fewer (so that the last bits of a dialogue's result depend on the
+ * other dialogues' lengths), and that size has room for them; a smaller
+ * workspace, down to batch * hq * splits * (d + 2) * 4 bytes (rounded up)
+ * with one chunk per 256 keys, at most 64, or num_splits, is accepted and
+ * cuts fewer. */
 ism_status ism_attn_decode(const void *q, const void *k_new, const void *v_new,
                            void *k_cache, void *v_cache, int32_t cache_cap,
                            const int32_t *cache_seqlens, int32_t batch,

@@ -20,9 +20,9 @@ namespace {
 using ism::align_up;
 using ism::fail;
 using ism::kAlign;
-using ism::PrefillKind;
 using ism::prefill_kind;
 using ism::split_plan;
+using ism::SplitKind;
 using ism::SplitPlan;
 
 // Device check, cached per device ordinal: a gfx950 device must be current.
@@ -178,7 +178,7 @@ size_t decode_min_workspace(int32_t batch, int32_t max_len, int32_t hq, int32_t 
 
 void apply_plan(ism::SplitArgs &a, const SplitPlan &p, int32_t fixed, void *ws) {
   a.colw = p.colw; a.col_groups = p.col_groups; a.col_stride = p.col_stride;
-  a.budget = p.budget; a.inv_budget = 1.0001f / (float)p.budget;
+  a.budget = p.budget;
   a.max_units = p.max_units; a.max_splits = p.max_splits;
   a.min_tiles = p.min_tiles; a.tile_shift = p.tile_shift; a.fixed_splits = fixed;
   a.part_o = (float *)ws;
@@ -243,7 +243,7 @@ extern "C" size_t ism_attn_prefill_workspace_size(int32_t batch, int32_t total_n
   if (batch < 1 || total_new < 1 || max_new < 1 || hkv < 1 || hq < hkv || hq % hkv || d < 1 ||
       cache_cap < 1)
     return 0;
-  const PrefillKind kind = prefill_kind(batch, total_new, max_new, hq, hkv);
+  const SplitKind kind = prefill_kind(batch, total_new, max_new, hq, hkv);
   return kind == ism::kRowTiles ? 0
                                 : split_plan(kind, batch, total_new, max_new, hq, hkv, d,
                                              cache_cap, 0, false, 0).bytes();
@@ -423,7 +423,7 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
   const size_t split_need =
       ism_attn_prefill_workspace_size(batch, total_new, max_new, hq, hkv, d, cache_cap);
   // (no need: short caches, one chunk per dialogue)
-  const PrefillKind kind =
+  const SplitKind kind =
       split_need == 0 || (ws && (uintptr_t)ws % kAlign == 0 && ws_bytes >= split_need)
           ? prefill_kind(batch, total_new, max_new, hq, hkv)
           : ism::kRowTiles;
@@ -682,10 +682,10 @@ namespace {
 // It holds the whole plan of every step that is accepted (whose smallest
 // workspace is at most ISM_NOALLOC_SCRATCH_BYTES), so that the step cuts the
 // keys as ism_attn_decode does with its recommended workspace: the plan's
-// partials are those of at most 640 (d = 128) or 960 chunks of 32 columns,
-// hq more, and 2 batch hq (column groups of 32 more than fill half), of
-// (d + 2) * 4 bytes each, where batch hq (d + 2) * 4 is at most that limit and
-// hq at most 8192: 31.9e6 bytes.
+// partials are those of 1024 units of 32 columns, or of 9/8 of the whole
+// dialogues' columns and 256 such units, of (d + 2) * 4 bytes each, where batch
+// hq (d + 2) * 4 is at most that limit and the columns are at most 2 batch hq
+// (groups of 32, more than half of them filled): 23.2e6 bytes.
 constexpr size_t kScratchBytes = 32u << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

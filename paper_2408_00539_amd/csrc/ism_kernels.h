@@ -169,12 +169,11 @@ struct SplitArgs {
   int32_t colw;              // columns (row, head) per workgroup: 32, or 128 (row-tiled)
   int32_t col_groups;        // column groups of the longest dialogue
   int32_t col_stride;        // columns per partials slot
-  int32_t budget;            // units (chunk, column group) per KV head to aim at
-  float inv_budget;          // 1 / budget, rounded up a little
+  int32_t budget;            // units (chunk, column group) per KV head at most (0: any fit)
   int32_t max_units;         // bound of the units per KV head
   int32_t max_splits;        // chunks per dialogue at most
   int32_t tile_shift;        // log2 of the keys per tile (32 or 64)
-  int32_t min_tiles;         // tiles per chunk at least (automatic plan)
+  int32_t min_tiles;         // tiles that chunks are cut for at least (automatic plan)
   int32_t fixed_splits;      // > 0: that many chunks per dialogue
   // paged cache (see FwdArgs)
   const int32_t *block_table;

@@ -55,15 +55,16 @@ __device__ __forceinline__ int groups_of(const SplitArgs &a, int rows) {
   return min((int)(((int64_t)rows * a.group + a.colw - 1) >> (a.colw == 32 ? 5 : 7)), a.col_groups);
 }
 
-// a / b (a >= 0, b >= 1) through the hardware reciprocal: exact for
-// a < 2^22, where the estimate is at most one off, else the long division.
-// (The plan is a serial chain at the start of every workgroup.)
+// a / b (a >= 0, b >= 1) through the hardware reciprocal, exact: the first
+// estimate is at most a >> 21 (or one) off, so that what remains over b is
+// below 2^22 and the second is at most one off. (The plan is a serial chain at
+// the start of every workgroup; an integer division is 40 instructions.)
 __device__ __forceinline__ int quot(int a, int b) {
-  if (a >= 1 << 22) return a / b;
-  int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  const float inv = __builtin_amdgcn_rcpf((float)b);
+  int q = (int)((float)a * inv);
+  q += (int)((float)(a - q * b) * inv);
   const int r = a - q * b;
-  q += r >= b ? 1 : r < 0 ? -1 : 0;
-  return q;
+  return q + (r >= b ? 1 : r < 0 ? -1 : 0);
 }
 
 // Tiles per chunk of a dialogue of t tiles, when chunks hold at most lc tiles
@@ -112,12 +113,75 @@ struct Unit {
   Extent x;
 };
 
-// The unit of workgroup `bid` (false: none). Chunk length: at least min_tiles,
-// and such that sum n_b groups_b <= budget + sum groups_b, which bounds the
-// grid on the host (the sum in fp32 and rounded up, the same in every
-// workgroup). Workgroups go round-robin to the 8 XCDs, so XCD x takes a
-// contiguous eighth of the units and the column groups that read the same
-// chunk share its L2.
+// Dialogue b's lengths, tiles and column groups (none past the batch).
+struct Entry {
+  RawLen r;
+  int t, g;
+};
+__device__ __forceinline__ Entry load_entry(const SplitArgs &a, int b) {
+  Entry x;
+  x.r = raw_len(a, min(b, a.batch - 1));
+  const Extent e = extent_from(a, x.r.r0, x.r.rows, x.r.cached);
+  x.t = b < a.batch ? tiles_of(a, e) : 0;
+  x.g = b < a.batch ? groups_of(a, e.rows) : 0;
+  return x;
+}
+// Up to 64 kWaves dialogues are held in registers, `lane`, `lane` + 64, ...
+constexpr int kWaves = 4;
+__device__ __forceinline__ int units_of(const SplitArgs &a, const Entry &x, int lc) {
+  return chunks_of(a, x.t, lc) * x.g;
+}
+
+// Tiles per chunk at most: a length for which the chunks of all dialogues,
+// sum n_b groups_b, are at most `budget`, which bounds the grid on the host
+// (budget >= sum groups_b, so that one chunk per dialogue always fits; the
+// same sums in every workgroup). A one-wave launch with its dialogues in
+// registers counts the chunks of each length tried: first the one that fills
+// the budget if every dialogue's last chunk is half full (equal dialogues then
+// get as many chunks as the budget holds), then lengths that make room for
+// what rounding up did add. Others take the length whose bound, sum t_b
+// groups_b / lc + sum groups_b, fits.
+__device__ __forceinline__ int chunk_limit(const SplitArgs &a, int lane, const Entry (&w)[kWaves]) {
+  constexpr int kLongest = 1 << 26;  // tiles: any dialogue is one chunk
+  float sum = (float)w[0].t * (float)w[0].g, groups = (float)w[0].g;
+  if (a.batch > 64)
+#pragma unroll
+    for (int i = 1; i < kWaves; ++i) {
+      sum += (float)w[i].t * (float)w[i].g;
+      groups += (float)w[i].g;
+    }
+  for (int b0 = 64 * kWaves; b0 < a.batch; b0 += 64) {
+    const Entry x = load_entry(a, b0 + lane);
+    sum += (float)x.t * (float)x.g;
+    groups += (float)x.g;
+  }
+  sum = wave_total(sum);
+  groups = wave_total(groups);
+  const float budget = (float)a.budget;
+  const bool count = a.colw == 32 && a.batch <= 64 * kWaves;
+  float units = budget - (count ? 0.5f : 1.f) * groups;
+  for (int lc = 0;;) {
+    // sum / units, rounded up
+    const float l = units >= 1.f ? sum * __builtin_amdgcn_rcpf(units) * 1.0001f : 1e9f;
+    const int next = __builtin_amdgcn_readfirstlane((int)fminf(l, (float)kLongest) + 1);
+    lc = max(max(next, a.min_tiles), lc ? lc + (lc >> 4) + 1 : 0);
+    if (!count) return lc;
+    auto most = [&](const Entry &x) __attribute__((always_inline)) {
+      return min(quot(x.t + lc - 1, lc), a.max_splits) * x.g;
+    };
+    int c = most(w[0]);
+    if (a.batch > 64)
+#pragma unroll
+      for (int i = 1; i < kWaves; ++i) c += most(w[i]);
+    c = __builtin_amdgcn_readlane(wave_scan(c), 63);
+    if (c <= a.budget || lc > kLongest) return lc;
+    units = budget - ((float)c - sum * __builtin_amdgcn_rcpf((float)lc));
+  }
+}
+
+// The unit of workgroup `bid` (false: none). Workgroups go round-robin to the
+// 8 XCDs, so XCD x takes a contiguous eighth of the units and the column
+// groups that read the same chunk share its L2.
 __device__ __forceinline__ bool find_unit(const SplitArgs &a, int bid, int lane, Unit &u) {
   if (a.max_splits == 1 && a.colw == 32) {
     // One chunk per dialogue and the same column groups in each (a one-wave
@@ -138,70 +202,69 @@ __device__ __forceinline__ bool find_unit(const SplitArgs &a, int bid, int lane,
     u.tiles = __builtin_amdgcn_readfirstlane(tiles_of(a, u.x));
     return u.tiles > 0;
   }
-  RawLen r{0, 0, 0};  // dialogue `lane` (kept: most batches fit one wave)
-  int t = 0, g = 0;
-  auto load = [&](int b) __attribute__((always_inline)) {
-    t = 0;
-    g = 0;
-    if (b < a.batch) {
-      r = raw_len(a, b);
-      const Extent x = extent_from(a, r.r0, r.rows, r.cached);
-      t = tiles_of(a, x);
-      g = groups_of(a, x.rows);
-    }
-  };
-  load(lane);
-  int lc = 1;
-  if (!a.fixed_splits && a.max_splits > 1) {
-    float sum = (float)t * (float)g;
-    if (a.batch > 64) {
-      for (int b0 = 64; b0 < a.batch; b0 += 64) {
-        load(b0 + lane);
-        sum += (float)t * (float)g;
-      }
-      load(lane);
-    }
-    const float per = wave_total(sum) * a.inv_budget;
-    lc = __builtin_amdgcn_readfirstlane(max((int)fminf(per, 1e9f) + 1, a.min_tiles));
-  }
+  Entry w[kWaves] = {load_entry(a, lane)};
+  if (a.batch > 64)
+#pragma unroll
+    for (int i = 1; i < kWaves; ++i) w[i] = load_entry(a, 64 * i + lane);
+  const int lc = a.fixed_splits || a.max_splits == 1 ? 1
+                 : a.budget                          ? chunk_limit(a, lane, w)
+                                                     : a.min_tiles;
   // the units of all dialogues (per KV head), then this workgroup's among
-  // them: one scan when the batch fits one wave
-  int cnt = chunks_of(a, t, lc) * g, inc = wave_scan(cnt);
-  int all = __builtin_amdgcn_readlane(inc, 63);
-  for (int b0 = 64; b0 < a.batch; b0 += 64) {
-    load(b0 + lane);
-    all += __builtin_amdgcn_readlane(wave_scan(chunks_of(a, t, lc) * g), 63);
-  }
+  // them: by wave of 64 dialogues, then one scan
+  int cnt[kWaves], inc[kWaves], all = 0;
+#pragma unroll
+  for (int i = 0; i < kWaves; ++i)
+    if (i == 0 || a.batch > 64) {
+      cnt[i] = units_of(a, w[i], lc);
+      inc[i] = wave_scan(cnt[i]);
+      all += __builtin_amdgcn_readlane(inc[i], 63);
+    }
+  for (int b0 = 64 * kWaves; b0 < a.batch; b0 += 64)
+    all += __builtin_amdgcn_readlane(wave_scan(units_of(a, load_entry(a, b0 + lane), lc)), 63);
   // (never more than the host made room for, whatever the length arrays say)
   const int units = min(all, a.max_units) * a.hkv, per_xcd = (units + 7) >> 3;
   const int i = bid >> 3, flat = (bid & 7) * per_xcd + i;
   if (i >= per_xcd || flat >= units) return false;
-  int base = 0, b0 = 0;
-  if (a.batch > 64) {  // the wave of dialogues that holds it
-    for (;; b0 += 64) {
-      load(b0 + lane);
-      cnt = chunks_of(a, t, lc) * g;
-      inc = wave_scan(cnt);
-      const int here = __builtin_amdgcn_readlane(inc, 63);
-      if (flat < (base + here) * a.hkv || b0 + 64 >= a.batch) break;
-      base += here;
+  int base = 0, b0 = 0, n = cnt[0], up = inc[0];
+  Entry e = w[0];
+  if (a.batch > 64) {
+#pragma unroll
+    for (int j = 1; j < kWaves; ++j) {
+      const int next = base + __builtin_amdgcn_readlane(up, 63);
+      if (b0 == 64 * (j - 1) && flat >= next * a.hkv && 64 * j < a.batch) {
+        base = next;
+        b0 = 64 * j;
+        n = cnt[j];
+        up = inc[j];
+        e = w[j];
+      }
+    }
+    for (int b = 64 * kWaves; b < a.batch; b += 64) {
+      const int next = base + __builtin_amdgcn_readlane(up, 63);
+      if (b0 != b - 64 || flat < next * a.hkv) break;
+      base = next;
+      b0 = b;
+      e = load_entry(a, b + lane);
+      n = units_of(a, e, lc);
+      up = wave_scan(n);
     }
   }
-  const int src = __builtin_ctzll(__builtin_amdgcn_ballot_w64((base + inc) * a.hkv > flat));
-  const int first = base + __builtin_amdgcn_readlane(inc - cnt, src);
-  const int gs = __builtin_amdgcn_readlane(g, src);
+  const int src = __builtin_ctzll(__builtin_amdgcn_ballot_w64((base + up) * a.hkv > flat));
+  const int first = base + __builtin_amdgcn_readlane(up - n, src);
+  const int gs = __builtin_amdgcn_readlane(e.g, src);
   u.b = __builtin_amdgcn_readfirstlane(b0 + src);
-  u.n = __builtin_amdgcn_readfirstlane(quot(__builtin_amdgcn_readlane(cnt, src), gs));
+  u.n = __builtin_amdgcn_readfirstlane(quot(__builtin_amdgcn_readlane(n, src), gs));
   const int j = flat - first * a.hkv;  // chunk-major, then KV head, column group
   u.split = __builtin_amdgcn_readfirstlane(quot(j, gs * a.hkv));
   const int k = j - u.split * gs * a.hkv;
   u.kvh = __builtin_amdgcn_readfirstlane(quot(k, gs));
   u.cg = k - u.kvh * gs;
   u.slot = flat;
-  u.x = extent_from(a, __builtin_amdgcn_readlane(r.r0, src), __builtin_amdgcn_readlane(r.rows, src),
-                    __builtin_amdgcn_readlane(r.cached, src));
+  u.x = extent_from(a, __builtin_amdgcn_readlane(e.r.r0, src),
+                    __builtin_amdgcn_readlane(e.r.rows, src),
+                    __builtin_amdgcn_readlane(e.r.cached, src));
   u.x.keys = __builtin_amdgcn_readfirstlane(u.x.keys);  // (formed with vector instructions)
-  const int t_all = __builtin_amdgcn_readlane(t, src);
+  const int t_all = __builtin_amdgcn_readlane(e.t, src);
   const int per = __builtin_amdgcn_readfirstlane(chunk_len(a, t_all, lc));
   u.tile0 = u.split * per;
   u.tiles = min(per, t_all - u.tile0);

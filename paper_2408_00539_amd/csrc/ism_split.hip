@@ -13,20 +13,18 @@
 //  * units (ism_plan.h): a dialogue's keys are cut into chunks of whole 32-key
 //    tiles at about the same length in every dialogue, so that ragged
 //    dialogues load the chip evenly; equal chunk counts per dialogue left the
-//    longest dialogue's chunks running alone (40 dialogues of 200 to 4000
-//    keys, 32 / 8 heads, pages of 64: 78 us, now 61; 24 dialogues of 1500 to
-//    6000 keys, 8 drafted rows: 118 us in the forward kernel, now 79).
+//    longest dialogue's chunks running alone (a step of 40 dialogues of 200 to
+//    4000 keys, 32 / 8 heads, pages of 64: 79.6 us, now 66.4; 24 dialogues of
+//    1500 to 6000 keys, 8 drafted rows, pages of 256: 117.4 us in the forward
+//    kernel, now 82.7; d = 64, 64 / 8 heads, 40 dialogues of 400 to 9000 keys
+//    104 us, now 67; equal dialogues were and are at the same rate).
 //  * a dialogue cut into one chunk writes its output directly; otherwise
 //    each unit writes unnormalised fp32 partials (m, l, o), merged exactly by
 //    split_combine_kernel.
 // A wave streams its chunk through a ring of two K/V tiles in LDS (direct
 // global->LDS transfers; at d = 128 a third stage measured the same at the
-// same number of workgroups and leaves room for fewer). About 640 units at
-// d = 128: 68 us for the first call above, against 73 with 512 and 71 with
-// 768 (with the combine). At d = 64 a wave spends longer per byte, and 960
-// units: 81 us for 40 ragged dialogues of up to 9000 keys, 64 / 8 heads,
-// against 108 with the equal splits before (30 equal dialogues of 5000 keys,
-// 16 / 8 heads: 52 against 50; 1280 units 55, and 73 on the ragged ones).
+// same number of workgroups and leaves room for fewer). How many units a call
+// is cut into: ism_split_plan.h.
 // The new rows' keys and values are read from the input, and the unit whose
 // tile holds them stores them into the cache, so that no append launch runs
 // first (the rotating append of 2-D positions does).

@@ -11,20 +11,20 @@ namespace ism {
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// How a cached prefill runs: kOneWave when the (row, query head) pairs of the
-// longest new segment that share a KV head fill at most one 32-column block,
-// so that the cache is streamed once (two blocks would stream it twice: the
-// row-tiled forward kernel shares its K/V tiles among four waves); else the
-// forward kernel, its key ranges split into about 448 units when its
-// workgroups leave most of the 512 that fit the chip unused. Measured
-// unsplit against split (us), by workgroups: 32 (8 ragged dialogues up to
-// 12000 keys, 16 rows, 32/2 heads) 172, 43; 32 (1 x 4000, 100 rows, 32/8) 64,
-// 31; 160 (10 x 3000, 50 rows, 32/8) 61, 55; 236 (8 ragged up to 3000, 200
-// rows, 32/2) 83, 114; 320 (20 ragged up to 4000, 60 rows, 32/8) 95, 120: the
-// partials of that many rows cost more than the idle workgroups.
-enum PrefillKind { kRowTiles, kRowTilesSplit, kOneWave };
-inline PrefillKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_new, int32_t hq,
-                                int32_t hkv) {
+// How a call over the cache runs. A decode step: the split-key kernel. A
+// cached prefill: the same kernel (kOneWave) when the (row, query head) pairs
+// of the longest new segment that share a KV head fill at most one 32-column
+// block, so that the cache is streamed once (two blocks would stream it
+// twice: the row-tiled forward kernel shares its K/V tiles among four waves);
+// else the forward kernel, its key ranges split when its workgroups leave
+// most of the 512 that fit the chip unused. Measured unsplit against split (us), by workgroups: 32 (8 dialogues
+// of 2000 to 12000 keys, 16 rows, 32/2 heads) 170, 37; 32 (1 x 4000, 100 rows,
+// 32/8) 63, 33; 160 (10 x 3000, 50 rows, 32/8) 61, 55; 236 (8 ragged up to
+// 3000, 200 rows, 32/2) 83, 114; 320 (20 ragged up to 4000, 60 rows, 32/8) 95,
+// 120: the partials of that many rows cost more than the idle workgroups.
+enum SplitKind { kRowTiles, kRowTilesSplit, kOneWave };
+inline SplitKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_new, int32_t hq,
+                              int32_t hkv) {
   const int64_t g = hq / hkv;
   if (max_new * g <= 32) return kOneWave;
   const int64_t wgs = hkv * (total_new * g / 128 + batch);
@@ -32,11 +32,10 @@ inline PrefillKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_ne
 }
 
 // The columns of a workgroup and how many units to make. The kernel decides
-// the shape: one-wave workgroups of 32 columns and 32-key tiles (kOneWave,
-// and every decode step: ism_split.hip, where the unit counts are measured),
+// the shape: one-wave workgroups of 32 columns and 32-key tiles (ism_split.hip)
 // or the forward kernel's of 128 columns and 64-key tiles. A chunk is cut for
-// at least min_tiles tiles (the chunks of a dialogue are then evened out, so
-// a short dialogue's may hold fewer); at most 64 chunks.
+// at least min_tiles tiles, 128 or 256 keys (the chunks of a dialogue are then
+// evened out, so those of a short dialogue can be smaller); at most 64 chunks.
 struct SplitPlan {
   int32_t colw, col_groups, col_stride, budget, max_units, max_splits, tile_shift, min_tiles;
   // workspace of the partials and the plan (0: one chunk per dialogue)
@@ -44,17 +43,28 @@ struct SplitPlan {
   size_t bytes() const { return part_bytes + ml_bytes + plan_bytes; }
 };
 
-constexpr int kSplitUnits = 640, kSplitUnits64 = 960, kSplitUnits128 = 448;
-// From this many (dialogue, KV head, column group) workgroups on (1280 one-wave
-// workgroups fit the chip), a one-wave launch keeps every dialogue whole and
-// needs no plan, whose scans over many dialogues every workgroup would repeat.
-// Measured with the plan and without (us): decode, 32/8 heads, 256 ragged
-// dialogues up to 1000 keys 106.3, 101.6; 1000: 404, 347; 2000: 1080, 845; 8
-// drafted rows over 300 ragged up to 800 keys 128, 114; 64/8 heads, d 64, 256
-// x 300 keys 34.9, 28.1. Below it, splitting the long dialogues of a ragged
-// batch is worth the plan.
+// Units of all KV heads at most, which is also the grid: the one-wave
+// workgroups that the chip holds at once at d = 128 (four to a CU by their
+// LDS), so that the last chunks don't start when the first end, and no
+// surplus workgroups pass through the CUs (a surplus left some SIMDs with two
+// of a call's waves, which then end last: 800 units with 640 surplus workgroups
+// 589 us, without 544). With 768, 1024, 1152 units (us): decode, 32/8 heads, 40
+// ragged dialogues up to 4000 keys 61.4, 60.4, 68.6; 64 ragged up to 4000
+// 107, 103, 119; 64 x 4000 169, 165, 175; 100 x 8192 (800 units whole) 611,
+// 561, 606. Partials of 17 columns and more weigh more (8 rows, 32/8 heads, 8 x
+// 3000 29.5, 31.9, 32.1; decode, 32/1 heads, 16 x 8192 26.5, 29.3, -), so those
+// take 768 while dialogues need cutting. A call that fills the chip with whole
+// dialogues has an eighth of them and 256 more for the long ones. Row-tiled
+// launches, whose partials weigh most, cut for 448 units (two to a CU).
+constexpr int kSplitUnits = 1024, kSplitUnits32 = 768, kSplitUnits128 = 448;
+// From this many (dialogue, KV head, column group) workgroups on, a one-wave
+// launch keeps every dialogue whole and needs no plan, whose scans over many
+// dialogues every workgroup would repeat. Measured with the plan and without
+// (us): decode, 32/8 heads, 256 x 1000 keys 175, 170; 1000 x 300 276, 204; 2000
+// ragged up to 500 682, 355; 64/8 heads, d 64, 256 x 300 34.6, 28.1; 8 drafted
+// rows, 32/8 heads, 256 ragged up to 1000 136, 123; 500 x 300 150, 125.
 constexpr int kSplitDirect = 2048;
-inline SplitPlan split_plan(PrefillKind kind, int32_t batch, int64_t total_rows, int32_t max_rows,
+inline SplitPlan split_plan(SplitKind kind, int32_t batch, int64_t total_rows, int32_t max_rows,
                             int32_t hq, int32_t hkv, int32_t d, int64_t max_len, int32_t fixed,
                             bool limited, size_t ws_bytes) {
   SplitPlan p{};
@@ -65,8 +75,6 @@ inline SplitPlan split_plan(PrefillKind kind, int32_t batch, int64_t total_rows,
   p.min_tiles = 4;
   p.col_groups = (int32_t)((cols + p.colw - 1) / p.colw);
   p.col_stride = (int32_t)(cols < p.colw ? cols : p.colw);
-  const int target = !one_wave ? kSplitUnits128 : d == 64 ? kSplitUnits64 : kSplitUnits;
-  p.budget = (target + hkv - 1) / hkv;
   const int64_t tiles = (max_len + (1 << p.tile_shift) - 1) >> p.tile_shift;
   const int64_t most = fixed > 0 ? fixed : (tiles + p.min_tiles - 1) / p.min_tiles;
   p.max_splits = (int32_t)(most < 1 ? 1 : fixed <= 0 && most > 64 ? 64 : most);
@@ -77,8 +85,14 @@ inline SplitPlan split_plan(PrefillKind kind, int32_t batch, int64_t total_rows,
   const int64_t by_rows = total_rows * (hq / hkv) / p.colw + batch, groups = p.col_groups;
   const int64_t all_groups = by_rows < (int64_t)batch * groups ? by_rows : (int64_t)batch * groups;
   const int64_t per = (int64_t)hkv * p.col_stride * (d + 2) * 4;
+  const int64_t whole = all_groups * hkv;  // units if no dialogue is cut
+  int64_t target = p.col_stride > 16 && whole <= 512 ? kSplitUnits32 : kSplitUnits;
+  if (whole >= target) target = whole + whole / 8 + 256;
+  if (!one_wave) target = whole + kSplitUnits128;
+  p.budget = (int32_t)(target / hkv);
   int64_t units = all_groups * p.max_splits;
-  if (fixed <= 0 && units > (int64_t)p.budget + all_groups) units = (int64_t)p.budget + all_groups;
+  if (fixed <= 0 && units > p.budget) units = p.budget;
+  else if (one_wave) p.budget = 0;
   auto layout = [&](int64_t n) {
     p.max_units = (int32_t)n;
     p.part_bytes = align_up((size_t)n * hkv * p.col_stride * d * 4);
@@ -94,7 +108,7 @@ inline SplitPlan split_plan(PrefillKind kind, int32_t batch, int64_t total_rows,
       p.max_splits = (int32_t)(fit / all_groups);
       layout(all_groups * p.max_splits);
     } else if (fixed <= 0 && fit > all_groups) {
-      p.budget = (int32_t)(fit - all_groups);
+      p.budget = (int32_t)fit;
       layout(fit);
     } else {
       p.max_splits = 1;

@@ -36,17 +36,25 @@ def _hist(rng, batch, longest):
     (70, 300, 4, 1, 128, 4, False),     # more dialogues than lanes
     (130, 90, 2, 2, 64, 3, True),
     (260, 70, 16, 8, 64, 3, False),     # 2080 workgroups: whole dialogues, no plan
+    # more chunks wanted than the chip holds, so that their length is searched:
+    # one wave of dialogues, two, three, more than the registers hold
+    (40, 2100, 8, 8, 64, 8, False),
+    (70, 1500, 8, 8, 64, 4, True),
+    (130, 700, 16, 8, 64, 3, False),
+    (300, 500, 2, 1, 64, 3, False),
     # the row-tiled kernel over split key ranges: chunks that some or all rows
     # of a workgroup end before, several column groups, heads of a group of 3
     (4, 2100, 4, 1, 128, 150, False),
     (5, 1300, 2, 2, 64, 200, False),
     (11, 900, 16, 1, 64, 40, True),
     (3, 5000, 3, 1, 128, 33, False),
+    (8, 9000, 4, 4, 64, 100, False),
+    (11, 1100, 16, 1, 64, 40, True),
     # one new row whose heads alone fill more than one 32-column block
     (5, 4000, 40, 1, 64, 1, True),
     (4, 8000, 64, 1, 128, 1, False),
     (3, 4100, 160, 1, 64, 1, False),
-    (11, 900, 256, 1, 128, 1, True),
+    (11, 1100, 256, 1, 128, 1, True),
     (5, 1300, 512, 2, 128, 1, False),
 ])
 def test_ragged_chunks(batch, longest, hq, hkv, d, new, is_query):

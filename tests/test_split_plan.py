@@ -24,7 +24,7 @@ extern "C" int kind_of(int batch, long total, int rows, int hq, int hkv) {
 }
 extern "C" void plan_of(int kind, int batch, long total, int rows, int hq, int hkv, int d,
                         long max_len, int fixed, int limited, long ws, long *out) {
-  const ism::SplitPlan p = ism::split_plan((ism::PrefillKind)kind, batch, total, rows, hq, hkv, d,
+  const ism::SplitPlan p = ism::split_plan((ism::SplitKind)kind, batch, total, rows, hq, hkv, d,
                                            max_len, fixed, limited, ws);
   const long v[] = {p.colw, p.col_groups, p.col_stride, p.budget, p.max_units, p.max_splits,
                     p.tile_shift, p.min_tiles, (long)p.part_bytes, (long)p.ml_bytes,
@@ -71,18 +71,32 @@ def units(p, cached, rows, group, cap, fixed=0):
     keys = np.clip(cached.astype(np.int64) + rows, 1, cap)
     t = np.where(rows > 0, ((keys - 1) >> p.tile_shift) + 1, 0)
     g = np.minimum(-(-rows.astype(np.int64) * group // p.colw), p.col_groups)
+    def chunks(lc):
+        n = np.minimum(fixed or -(-t // lc), p.max_splits)
+        per = np.where(n <= 1, np.maximum(t, 1), -(-t // np.maximum(n, 1)))
+        return per, -(-t // per)
+
     lc = 1
-    if not fixed and p.max_splits > 1:
-        s = np.float32((t * g).sum())
-        per = s * (np.float32(1.0001) / np.float32(p.budget))
-        lc = max(int(per) + 1, p.min_tiles)
+    if not fixed and p.max_splits > 1 and not p.budget:
+        lc = p.min_tiles
+    elif not fixed and p.max_splits > 1:
+        total, longest = np.float32((t * g).sum()), 1 << 26
+
+        groups, lc, count = int(g.sum()), 0, p.colw == 32 and len(rows) <= 256
+        room = p.budget - groups * (0.5 if count else 1)
+        while True:
+            x = np.float32(total / np.float32(max(room, 1)) * np.float32(1.0001))
+            lc = max(int(min(x if room >= 1 else 1e9, longest)) + 1, p.min_tiles,
+                     lc + (lc >> 4) + 1 if lc else 0)
+            c = int((np.minimum(-(-t // lc), p.max_splits) * g).sum())
+            if not count or c <= p.budget or lc > longest:
+                break
+            room = p.budget - (c - float(total) / lc)
+    per, n = chunks(lc)
     out = []
     for b in range(len(rows)):
-        n = min(fixed or -(-int(t[b]) // lc), p.max_splits)
-        per = max(int(t[b]), 1) if n <= 1 else -(-int(t[b]) // n)
-        n = -(-int(t[b]) // per)
-        out += [(b, i, n, i * per, min(per, int(t[b]) - i * per), int(keys[b]), int(g[b]))
-                for i in range(n)]
+        out += [(b, i, int(n[b]), i * int(per[b]), int(min(per[b], t[b] - i * per[b])),
+                 int(keys[b]), int(g[b])) for i in range(int(n[b]))]
     return out
 
 
@@ -114,15 +128,16 @@ def test_prefill_plan_fits_its_kernel(lib, rows):
     rng = np.random.default_rng(rows)
     kinds = set()
     for group in HEADS:
-        for hkv, batch in ((1, 1), (1, 3), (2, 11), (8, 70), (4, 600)):
-            kind = lib.kind_of(batch, rows * batch, rows, hkv * group, hkv)
-            if kind == ROW_TILES:
-                continue
-            kinds.add(kind)
-            for cap in (rows + 63, 4096, 8192, 200000):
+        for hkv, batch in ((1, 1), (1, 3), (2, 11), (8, 70), (16, 200), (4, 600)):
+            for cap in (rows + 63, 1025, 4096, 8192, 200000):
+                kind = lib.kind_of(batch, rows * batch, rows, hkv * group, hkv)
+                if kind == ROW_TILES:
+                    continue
+                kinds.add(kind)
                 p = Plan(lib, kind, batch, rows * batch, rows, hkv * group, hkv, 128, cap)
+                one_long = np.where(np.arange(batch) == batch // 2, cap - rows, cap // 100)
                 for cached in (np.full(batch, cap - rows), np.full(batch, max(0, cap // 2 - rows)),
-                               rng.integers(0, cap - rows + 1, size=batch)):
+                               rng.integers(0, cap - rows + 1, size=batch), one_long):
                     for new in (np.full(batch, rows), rng.integers(0, rows + 1, size=batch)):
                         check(p, kind, cached, new, hkv * group, hkv, 128, cap)
     assert ROW_TILES_SPLIT in kinds and (rows > 32 or ONE_WAVE in kinds)
@@ -130,7 +145,9 @@ def test_prefill_plan_fits_its_kernel(lib, rows):
 
 DECODES = [(1, 32, 8, 128, 2500), (1, 32, 8, 128, 8192), (9, 8, 2, 128, 3000),
            (9, 40, 1, 64, 3000), (4, 32, 8, 128, 3000), (40, 32, 8, 128, 4000),
-           (30, 16, 8, 64, 5000), (3, 64, 1, 128, 130), (200, 64, 8, 128, 900)]
+           (30, 16, 8, 64, 5000), (3, 64, 1, 128, 130), (200, 64, 8, 128, 900),
+           (101, 32, 8, 128, 32001), (256, 8, 4, 64, 4000), (300, 32, 2, 128, 4000),
+           (700, 24, 2, 64, 300), (5, 300, 100, 64, 9000)]
 
 
 @pytest.mark.parametrize("batch,hq,hkv,d,max_len", DECODES)
@@ -148,7 +165,9 @@ def test_decode_plan_in_its_workspace(lib, batch, hq, hkv, d, max_len, fixed):
             continue
         p = Plan(*args, ws=ws)
         assert p.bytes <= ws and p.max_units <= full.max_units
-        for cached in (np.full(batch, max_len - 1), rng.integers(0, max_len, size=batch)):
+        one_long = np.where(np.arange(batch) == batch // 2, max_len - 1, max_len // 100)
+        for cached in (np.full(batch, max_len - 1), rng.integers(0, max_len, size=batch),
+                       one_long):
             check(p, ONE_WAVE, cached, rows, hq, hkv, d, max_len, fixed)
 
 
@@ -175,3 +194,17 @@ def test_accepted_noalloc_steps_fit_the_scratch(lib):
                             most = max(most, p.bytes)
                             assert p.bytes <= scratch, (batch, hq, hkv, d, fixed, max_len)
     assert most > limit
+
+
+@pytest.mark.parametrize("batch,hkv,d", [(100, 8, 128), (64, 8, 128), (30, 8, 64), (127, 8, 128)])
+def test_equal_decodes_fill_their_grid(lib, batch, hkv, d):
+    """A step of equal dialogues launches no more workgroups than the chip
+    holds at once, and as many chunks as the grid has room for."""
+    rows = np.ones(batch, dtype=np.int64)
+    for keys in (900, 4001, 8193):
+        p = Plan(lib, ONE_WAVE, batch, batch, 1, 4 * hkv, hkv, d, keys)
+        assert p.max_units * hkv <= 1024
+        chunks = len(units(p, np.full(batch, keys - 1), rows, 4, keys)) // batch
+        most = min(p.max_units // batch, -(-keys // 128))
+        # (chunks of whole tiles: evening them out can drop some)
+        assert most == 1 and chunks == 1 or chunks > 0.7 * most
