@@ -226,7 +226,7 @@ extern "C" size_t ism_attn_workspace_size(int32_t op, int32_t batch,
     case ISM_OP_DECODE: {
       if (hkv < 1 || hq < hkv || hq % hkv) return 0;
       if (!ism::decode_vector(batch, hq, hkv)) {
-        const SplitPlan p = split_plan(ism::kOneWave, batch, batch, 1, hq, hkv, d, max_seqlen,
+        const SplitPlan p = split_plan(ism::kDecodeStep, batch, batch, 1, hq, hkv, d, max_seqlen,
                                        num_splits, false, 0);
         const size_t need = decode_min_workspace(batch, max_seqlen, hq, hkv, d, num_splits);
         return need > p.bytes() ? need : p.bytes();
@@ -612,7 +612,7 @@ ism_status decode_impl(const void *q, const void *k_new, const void *v_new, void
     a.total_q = batch; a.max_rows = 1;
     a.scale = scale;
     a.append = 1;
-    apply_plan(a, split_plan(ism::kOneWave, batch, batch, 1, hq, hkv, d, max_seqlen, num_splits,
+    apply_plan(a, split_plan(ism::kDecodeStep, batch, batch, 1, hq, hkv, d, max_seqlen, num_splits,
                              true, ws_bytes), num_splits, ws);
     if (pg) {
       a.block_table = pg->block_table;

@@ -22,7 +22,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // 32/8) 63, 33; 160 (10 x 3000, 50 rows, 32/8) 61, 55; 236 (8 ragged up to
 // 3000, 200 rows, 32/2) 83, 114; 320 (20 ragged up to 4000, 60 rows, 32/8) 95,
 // 120: the partials of that many rows cost more than the idle workgroups.
-enum SplitKind { kRowTiles, kRowTilesSplit, kOneWave };
+enum SplitKind { kRowTiles, kRowTilesSplit, kOneWave, kDecodeStep };
 inline SplitKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_new, int32_t hq,
                               int32_t hkv) {
   const int64_t g = hq / hkv;
@@ -62,14 +62,20 @@ constexpr int kSplitUnits = 1024, kSplitUnits32 = 768, kSplitUnits128 = 448;
 // dialogues every workgroup would repeat. Measured with the plan and without
 // (us): decode, 32/8 heads, 256 x 1000 keys 175, 170; 1000 x 300 276, 204; 2000
 // ragged up to 500 682, 355; 64/8 heads, d 64, 256 x 300 34.6, 28.1; 8 drafted
-// rows, 32/8 heads, 256 ragged up to 1000 136, 123; 500 x 300 150, 125.
-constexpr int kSplitDirect = 2048;
+// rows, 32/8 heads, 256 ragged up to 1000 136, 123; 500 x 300 150, 125. One wave
+// then streams a dialogue's keys at 45 per us, which decides the call when one
+// dialogue is many times the mean, and for drafted rows the forward kernel's
+// four waves, which served them before, had 63: one of 32000 keys among 255 of
+// 300 119 planned, 705 whole, 508 before. Prefills whose cache has room for
+// such a dialogue (90 us and more) therefore keep the plan up to the 256
+// dialogues that it holds in registers.
+constexpr int kSplitDirect = 2048, kSplitDirectKeys = 4096;
 inline SplitPlan split_plan(SplitKind kind, int32_t batch, int64_t total_rows, int32_t max_rows,
                             int32_t hq, int32_t hkv, int32_t d, int64_t max_len, int32_t fixed,
                             bool limited, size_t ws_bytes) {
   SplitPlan p{};
   const int64_t cols = (int64_t)max_rows * (hq / hkv);
-  const bool one_wave = kind == kOneWave;
+  const bool one_wave = kind == kOneWave || kind == kDecodeStep;
   p.colw = one_wave ? 32 : 128;
   p.tile_shift = one_wave ? 5 : 6;
   p.min_tiles = 4;
@@ -78,7 +84,8 @@ inline SplitPlan split_plan(SplitKind kind, int32_t batch, int64_t total_rows, i
   const int64_t tiles = (max_len + (1 << p.tile_shift) - 1) >> p.tile_shift;
   const int64_t most = fixed > 0 ? fixed : (tiles + p.min_tiles - 1) / p.min_tiles;
   p.max_splits = (int32_t)(most < 1 ? 1 : fixed <= 0 && most > 64 ? 64 : most);
-  if (one_wave && fixed <= 0 && (int64_t)batch * hkv * p.col_groups >= kSplitDirect)
+  if (one_wave && fixed <= 0 && (int64_t)batch * hkv * p.col_groups >= kSplitDirect &&
+      (kind == kDecodeStep || batch > 256 || max_len <= kSplitDirectKeys))
     p.max_splits = 1;
   // column groups of all dialogues together, partials of one unit over all
   // KV heads

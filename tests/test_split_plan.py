@@ -32,9 +32,9 @@ extern "C" void plan_of(int kind, int batch, long total, int rows, int hq, int h
   for (int i = 0; i < 11; ++i) out[i] = v[i];
 }
 """
-ROW_TILES, ROW_TILES_SPLIT, ONE_WAVE = 0, 1, 2
-COLS = {ROW_TILES_SPLIT: 128, ONE_WAVE: 32}
-KEYS = {ROW_TILES_SPLIT: 64, ONE_WAVE: 32}
+ROW_TILES, ROW_TILES_SPLIT, ONE_WAVE, DECODE = 0, 1, 2, 3
+COLS = {ROW_TILES_SPLIT: 128, ONE_WAVE: 32, DECODE: 32}
+KEYS = {ROW_TILES_SPLIT: 64, ONE_WAVE: 32, DECODE: 32}
 
 
 class Plan:
@@ -156,7 +156,7 @@ def test_decode_plan_in_its_workspace(lib, batch, hq, hkv, d, max_len, fixed):
     """With a workspace of the plan's own size it is the plan without a limit;
     smaller ones give plans that fit them."""
     rng = np.random.default_rng(batch + fixed)
-    args = (lib, ONE_WAVE, batch, batch, 1, hq, hkv, d, max_len, fixed)
+    args = (lib, DECODE, batch, batch, 1, hq, hkv, d, max_len, fixed)
     full = Plan(*args)
     assert Plan(*args, ws=full.bytes).key == full.key
     rows = np.ones(batch, dtype=np.int64)
@@ -168,7 +168,7 @@ def test_decode_plan_in_its_workspace(lib, batch, hq, hkv, d, max_len, fixed):
         one_long = np.where(np.arange(batch) == batch // 2, max_len - 1, max_len // 100)
         for cached in (np.full(batch, max_len - 1), rng.integers(0, max_len, size=batch),
                        one_long):
-            check(p, ONE_WAVE, cached, rows, hq, hkv, d, max_len, fixed)
+            check(p, DECODE, cached, rows, hq, hkv, d, max_len, fixed)
 
 
 def test_accepted_noalloc_steps_fit_the_scratch(lib):
@@ -190,7 +190,7 @@ def test_accepted_noalloc_steps_fit_the_scratch(lib):
                         if batch < 1 or batch * hq * max(fixed, 1) * (d + 2) * 4 > limit:
                             continue
                         for max_len in (1, 700, 8192, 1 << 20):
-                            p = Plan(lib, ONE_WAVE, batch, batch, 1, hq, hkv, d, max_len, fixed)
+                            p = Plan(lib, DECODE, batch, batch, 1, hq, hkv, d, max_len, fixed)
                             most = max(most, p.bytes)
                             assert p.bytes <= scratch, (batch, hq, hkv, d, fixed, max_len)
     assert most > limit
@@ -202,9 +202,20 @@ def test_equal_decodes_fill_their_grid(lib, batch, hkv, d):
     holds at once, and as many chunks as the grid has room for."""
     rows = np.ones(batch, dtype=np.int64)
     for keys in (900, 4001, 8193):
-        p = Plan(lib, ONE_WAVE, batch, batch, 1, 4 * hkv, hkv, d, keys)
+        p = Plan(lib, DECODE, batch, batch, 1, 4 * hkv, hkv, d, keys)
         assert p.max_units * hkv <= 1024
         chunks = len(units(p, np.full(batch, keys - 1), rows, 4, keys)) // batch
         most = min(p.max_units // batch, -(-keys // 128))
         # (chunks of whole tiles: evening them out can drop some)
         assert most == 1 and chunks == 1 or chunks > 0.7 * most
+
+
+def test_one_long_dialogue_among_many(lib):
+    """Drafted rows: a dialogue that decides the call is cut, also where whole
+    dialogues alone fill the chip; caches with no room for one need no plan."""
+    cached = np.array([32000] + [300] * 255)
+    rows = np.full(256, 8, dtype=np.int64)
+    p = Plan(lib, ONE_WAVE, 256, 2048, 8, 32, 8, 128, 32768)
+    u = units(p, cached, rows, 4, 32768)
+    assert max(x[4] for x in u) * KEYS[ONE_WAVE] < 4096
+    assert Plan(lib, ONE_WAVE, 256, 2048, 8, 32, 8, 128, 4096).max_splits == 1
