@@ -180,7 +180,7 @@ void apply_plan(ism::SplitArgs &a, const SplitPlan &p, int32_t fixed, void *ws) 
   a.colw = p.colw; a.col_groups = p.col_groups; a.col_stride = p.col_stride;
   a.budget = p.budget;
   a.max_units = p.max_units; a.max_splits = p.max_splits;
-  a.min_tiles = p.min_tiles; a.tile_shift = p.tile_shift; a.fixed_splits = fixed;
+  a.min_tiles = p.min_tiles; a.whole_tiles = p.whole_tiles; a.tile_shift = p.tile_shift; a.fixed_splits = fixed;
   a.part_o = (float *)ws;
   a.part_ml = (float *)((char *)ws + p.part_bytes);
   a.plan = p.max_splits > 1 ? (int32_t *)((char *)ws + p.part_bytes + p.ml_bytes) : nullptr;
@@ -243,7 +243,7 @@ extern "C" size_t ism_attn_prefill_workspace_size(int32_t batch, int32_t total_n
   if (batch < 1 || total_new < 1 || max_new < 1 || hkv < 1 || hq < hkv || hq % hkv || d < 1 ||
       cache_cap < 1)
     return 0;
-  const SplitKind kind = prefill_kind(batch, total_new, max_new, hq, hkv);
+  const SplitKind kind = prefill_kind(batch, total_new, max_new, hq, hkv, cache_cap);
   return kind == ism::kRowTiles ? 0
                                 : split_plan(kind, batch, total_new, max_new, hq, hkv, d,
                                              cache_cap, 0, false, 0).bytes();
@@ -425,7 +425,7 @@ ism_status prefill_impl(const int32_t *cu_seqlens_new, int32_t batch, int32_t to
   // (no need: short caches, one chunk per dialogue)
   const SplitKind kind =
       split_need == 0 || (ws && (uintptr_t)ws % kAlign == 0 && ws_bytes >= split_need)
-          ? prefill_kind(batch, total_new, max_new, hq, hkv)
+          ? prefill_kind(batch, total_new, max_new, hq, hkv, cache_cap)
           : ism::kRowTiles;
   if ((st = check_device())) return st;
   if ((st = validate_new_lengths(cu_seqlens_new, batch, total_new, max_new,

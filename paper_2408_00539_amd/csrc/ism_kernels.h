@@ -174,6 +174,7 @@ struct SplitArgs {
   int32_t max_splits;        // chunks per dialogue at most
   int32_t tile_shift;        // log2 of the keys per tile (32 or 64)
   int32_t min_tiles;         // tiles that chunks are cut for at least (automatic plan)
+  int32_t whole_tiles;       // dialogues of at most that many are one chunk
   int32_t fixed_splits;      // > 0: that many chunks per dialogue
   // paged cache (see FwdArgs)
   const int32_t *block_table;

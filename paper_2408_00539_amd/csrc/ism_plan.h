@@ -68,8 +68,10 @@ __device__ __forceinline__ int quot(int a, int b) {
 }
 
 // Tiles per chunk of a dialogue of t tiles, when chunks hold at most lc tiles
-// (or fixed_splits is set) and the chunks are as equal as whole tiles allow.
+// (or fixed_splits is set) and the chunks are as equal as whole tiles allow;
+// up to whole_tiles tiles are one chunk.
 __device__ __forceinline__ int chunk_len(const SplitArgs &a, int t, int lc) {
+  if (t <= a.whole_tiles) return max(t, 1);
   const int n = min(a.fixed_splits ? a.fixed_splits : quot(t + lc - 1, lc), a.max_splits);
   return n <= 1 ? max(t, 1) : quot(t + n - 1, n);
 }

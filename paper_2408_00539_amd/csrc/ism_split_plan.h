@@ -17,18 +17,22 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // block, so that the cache is streamed once (two blocks would stream it
 // twice: the row-tiled forward kernel shares its K/V tiles among four waves);
 // else the forward kernel, its key ranges split when its workgroups leave
-// most of the 512 that fit the chip unused. Measured unsplit against split (us), by workgroups: 32 (8 dialogues
+// most of the 512 that fit the chip unused and the cache is longer than two
+// chunks. Measured unsplit against split (us), by workgroups: 32 (8 dialogues
 // of 2000 to 12000 keys, 16 rows, 32/2 heads) 170, 37; 32 (1 x 4000, 100 rows,
 // 32/8) 63, 33; 160 (10 x 3000, 50 rows, 32/8) 61, 55; 236 (8 ragged up to
 // 3000, 200 rows, 32/2) 83, 114; 320 (20 ragged up to 4000, 60 rows, 32/8) 95,
-// 120: the partials of that many rows cost more than the idle workgroups.
+// 120: the partials of that many rows cost more than the idle workgroups. By
+// capacity: 768 (1 x 600, 100 rows, 32/8) 19.3, 21.0; 1024 (3 x 700, 64 rows)
+// 20.7, 24.7; 1280 (12 x 1000, 33 rows) 27.5, 26.7; 2304 (8 x 2000, 12 rows,
+// 64/8, d 64) 34.5, 23.5.
 enum SplitKind { kRowTiles, kRowTilesSplit, kOneWave, kDecodeStep };
 inline SplitKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_new, int32_t hq,
-                              int32_t hkv) {
+                              int32_t hkv, int32_t cache_cap) {
   const int64_t g = hq / hkv;
   if (max_new * g <= 32) return kOneWave;
   const int64_t wgs = hkv * (total_new * g / 128 + batch);
-  return wgs < 192 ? kRowTilesSplit : kRowTiles;
+  return wgs < 192 && cache_cap > 1024 ? kRowTilesSplit : kRowTiles;
 }
 
 // The columns of a workgroup and how many units to make. The kernel decides
@@ -36,8 +40,12 @@ inline SplitKind prefill_kind(int32_t batch, int64_t total_new, int32_t max_new,
 // or the forward kernel's of 128 columns and 64-key tiles. A chunk is cut for
 // at least min_tiles tiles, 128 or 256 keys (the chunks of a dialogue are then
 // evened out, so those of a short dialogue can be smaller); at most 64 chunks.
+// Row-tiled dialogues of up to 512 keys stay whole, as their rows' partials
+// cost more than the second chunk saves (cache of 8192, 4 x 300 keys, 40 rows,
+// 32 heads 19.4 whole, 21.1 us cut; 1 x 300, 200 rows, 32/8 20.4, 22.6).
 struct SplitPlan {
   int32_t colw, col_groups, col_stride, budget, max_units, max_splits, tile_shift, min_tiles;
+  int32_t whole_tiles;
   // workspace of the partials and the plan (0: one chunk per dialogue)
   size_t part_bytes, ml_bytes, plan_bytes;
   size_t bytes() const { return part_bytes + ml_bytes + plan_bytes; }
@@ -79,6 +87,7 @@ inline SplitPlan split_plan(SplitKind kind, int32_t batch, int64_t total_rows, i
   p.colw = one_wave ? 32 : 128;
   p.tile_shift = one_wave ? 5 : 6;
   p.min_tiles = 4;
+  p.whole_tiles = one_wave ? 0 : 8;
   p.col_groups = (int32_t)((cols + p.colw - 1) / p.colw);
   p.col_stride = (int32_t)(cols < p.colw ? cols : p.colw);
   const int64_t tiles = (max_len + (1 << p.tile_shift) - 1) >> p.tile_shift;

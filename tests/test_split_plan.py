@@ -19,17 +19,17 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
                     "paper_2408_00539_amd", "csrc")
 SHIM = """
 #include "ism_split_plan.h"
-extern "C" int kind_of(int batch, long total, int rows, int hq, int hkv) {
-  return ism::prefill_kind(batch, total, rows, hq, hkv);
+extern "C" int kind_of(int batch, long total, int rows, int hq, int hkv, int cap) {
+  return ism::prefill_kind(batch, total, rows, hq, hkv, cap);
 }
 extern "C" void plan_of(int kind, int batch, long total, int rows, int hq, int hkv, int d,
                         long max_len, int fixed, int limited, long ws, long *out) {
   const ism::SplitPlan p = ism::split_plan((ism::SplitKind)kind, batch, total, rows, hq, hkv, d,
                                            max_len, fixed, limited, ws);
   const long v[] = {p.colw, p.col_groups, p.col_stride, p.budget, p.max_units, p.max_splits,
-                    p.tile_shift, p.min_tiles, (long)p.part_bytes, (long)p.ml_bytes,
-                    (long)p.plan_bytes};
-  for (int i = 0; i < 11; ++i) out[i] = v[i];
+                    p.tile_shift, p.min_tiles, p.whole_tiles, (long)p.part_bytes,
+                    (long)p.ml_bytes, (long)p.plan_bytes};
+  for (int i = 0; i < 12; ++i) out[i] = v[i];
 }
 """
 ROW_TILES, ROW_TILES_SPLIT, ONE_WAVE, DECODE = 0, 1, 2, 3
@@ -39,12 +39,12 @@ KEYS = {ROW_TILES_SPLIT: 64, ONE_WAVE: 32, DECODE: 32}
 
 class Plan:
     def __init__(self, lib, kind, batch, total, rows, hq, hkv, d, max_len, fixed=0, ws=None):
-        out = (ctypes.c_long * 11)()
+        out = (ctypes.c_long * 12)()
         lib.plan_of(kind, batch, ctypes.c_long(total), rows, hq, hkv, d, ctypes.c_long(max_len),
                     fixed, ws is not None, ctypes.c_long(ws or 0), out)
         (self.colw, self.col_groups, self.col_stride, self.budget, self.max_units,
-         self.max_splits, self.tile_shift, self.min_tiles, self.part_bytes, self.ml_bytes,
-         self.plan_bytes) = out
+         self.max_splits, self.tile_shift, self.min_tiles, self.whole_tiles, self.part_bytes,
+         self.ml_bytes, self.plan_bytes) = out
         self.key = tuple(out)
         self.bytes = self.part_bytes + self.ml_bytes + self.plan_bytes
 
@@ -61,7 +61,7 @@ def lib(tmp_path_factory):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     out = ctypes.CDLL(str(d / "shim.so"))
-    out.kind_of.argtypes = [ctypes.c_int, ctypes.c_long] + 3 * [ctypes.c_int]
+    out.kind_of.argtypes = [ctypes.c_int, ctypes.c_long] + 4 * [ctypes.c_int]
     return out
 
 
@@ -72,7 +72,7 @@ def units(p, cached, rows, group, cap, fixed=0):
     t = np.where(rows > 0, ((keys - 1) >> p.tile_shift) + 1, 0)
     g = np.minimum(-(-rows.astype(np.int64) * group // p.colw), p.col_groups)
     def chunks(lc):
-        n = np.minimum(fixed or -(-t // lc), p.max_splits)
+        n = np.where(t <= p.whole_tiles, 1, np.minimum(fixed or -(-t // lc), p.max_splits))
         per = np.where(n <= 1, np.maximum(t, 1), -(-t // np.maximum(n, 1)))
         return per, -(-t // per)
 
@@ -130,7 +130,7 @@ def test_prefill_plan_fits_its_kernel(lib, rows):
     for group in HEADS:
         for hkv, batch in ((1, 1), (1, 3), (2, 11), (8, 70), (16, 200), (4, 600)):
             for cap in (rows + 63, 1025, 4096, 8192, 200000):
-                kind = lib.kind_of(batch, rows * batch, rows, hkv * group, hkv)
+                kind = lib.kind_of(batch, rows * batch, rows, hkv * group, hkv, cap)
                 if kind == ROW_TILES:
                     continue
                 kinds.add(kind)
@@ -219,3 +219,13 @@ def test_one_long_dialogue_among_many(lib):
     u = units(p, cached, rows, 4, 32768)
     assert max(x[4] for x in u) * KEYS[ONE_WAVE] < 4096
     assert Plan(lib, ONE_WAVE, 256, 2048, 8, 32, 8, 128, 4096).max_splits == 1
+
+
+def test_short_rows_stay_whole(lib):
+    """Row-tiled segments over short caches, or short dialogues in long ones,
+    are not cut."""
+    assert lib.kind_of(1, 200, 200, 32, 8, 1024) == ROW_TILES
+    assert lib.kind_of(1, 200, 200, 32, 8, 1088) == ROW_TILES_SPLIT
+    p = Plan(lib, ROW_TILES_SPLIT, 3, 120, 40, 32, 8, 128, 8192)
+    u = units(p, np.array([300, 472, 2000]), np.full(3, 40), 4, 8192)
+    assert [x[2] for x in u][:2] == [1, 1] and u[2][2] > 1
