@@ -53,6 +53,15 @@ namespace {
 
 constexpr int kBN = 64;  // keys per tile
 constexpr int kQW = 32;  // query rows per wave
+// Capacity from which a paged cache's transfers are spread over a step's
+// products like the dense cache's, instead of all starting with it. On long
+// key loops the burst costs four-wave workgroups more than eight-wave ones
+// paid (2048 new rows over 4 x 16384 keys, 32/8 heads, pages of 64 2468 us,
+// spread 2320, eight waves 2312; pages of 256 2260, 2142, 2209; 40 over 20 x
+// 8000, pages of 64 272, 235, 229); on short ones, where a tile's latency is
+// hidden by little else, an early start wins (64 over 40 x 2000, pages of 64
+// 133, spread 156).
+constexpr int kSpreadKeys = 8192;
 
 // Waves per SIMD, which bounds registers: d = 64 fits a third wave (4 x 8000
 // tokens, 16 heads: 420 -> 398 us; not the paged cache, which would spill).
@@ -186,8 +195,8 @@ __device__ __forceinline__ void tile_pv(const char *vl, const SwzOffsets<D> &so,
 // products and the exponentials, the vector-heavy half) and drops it for the
 // P V products, so that of the two waves on a SIMD the one in its
 // exponentials issues first and the other one's products fill the matrix
-// core around it (about 2 % faster on the packed forward; the paged cache,
-// whose transfers all start at the step start, measured ~1 % slower with it).
+// core around it (about 2 % faster on the packed forward; steps whose
+// transfers all start at the step start measured ~1 % slower with it).
 template <int D, bool LAST, bool PRIO, class Hook>
 __device__ __forceinline__ float step_block(const char *kl, const char *vl,
                                             const SwzOffsets<D> &so, const bf16x8 (&qf)[D / 16],
@@ -427,6 +436,9 @@ fwd_kernel(FwdArgs a, int fold, int tiles, int chunk, SplitArgs sp) {
   // paged cache: sources of K(t+2) and V(t+1) for step t
   const bf16_t *pk2 = PAGED ? tile_src(kbase, min(2, ntiles - 1)) : kt;
   const bf16_t *pv1 = PAGED ? tile_src(vbase, min(1, ntiles - 1)) : vt;
+  // its tiles per page, and those left in the pages of K(t+2) and V(t+1)
+  const int tpp = PAGED ? pg_size / kBN : 1, first = SPLIT ? key_begin / kBN : 0;
+  int kleft = PAGED ? tpp - (first + 2) % tpp : 0, vleft = PAGED ? tpp - (first + 1) % tpp : 0;
   SwzOffsets<D> so;
   so.init(lane);
 
@@ -471,7 +483,7 @@ fwd_kernel(FwdArgs a, int fold, int tiles, int chunk, SplitArgs sp) {
     };
     if (t < nw) {
       float mt;
-      l_run += step_block<D, LAST, !PAGED>(kl, vl, so, qf, cur, nxt, oacc, sl2,
+      l_run += step_block<D, LAST, !PAGED || MODE == 0>(kl, vl, so, qf, cur, nxt, oacc, sl2,
                                            log2_max<SPLIT>(m_run, sl2), mt, hook);
       if (!LAST && t + 1 < nw) {
         if (c0 + 2 * kBN - 1 > wave_lo) {  // S(t+1) crosses some row's bound
@@ -485,19 +497,19 @@ fwd_kernel(FwdArgs a, int fold, int tiles, int chunk, SplitArgs sp) {
       kt += tile_elems;
       vt += tile_elems;
       if constexpr (PAGED) {  // K(t+3) and V(t+2), re-based at page starts
-        const int tpp = pg_size / kBN, ta = (SPLIT ? key_begin / kBN : 0) + t;
-        pk2 = (ta + 3) % tpp ? pk2 + tile_elems : tile_src(kbase, min(t + 3, ntiles - 1));
-        pv1 = (ta + 2) % tpp ? pv1 + tile_elems : tile_src(vbase, min(t + 2, ntiles - 1));
+        const bool knew = --kleft == 0, vnew = --vleft == 0;
+        pk2 = knew ? tile_src(kbase, min(t + 3, ntiles - 1)) : pk2 + tile_elems;
+        pv1 = vnew ? tile_src(vbase, min(t + 2, ntiles - 1)) : pv1 + tile_elems;
+        if (knew) kleft = tpp;
+        if (vnew) vleft = tpp;
       }
     }
     wait_vmem();
     __syncthreads();
   };
   // steps whose K(t+2) and V(t+1) are full tiles, an even count of them
-  // (the paged cache looks up each tile's page at the step start and issues
-  // its transfers at once)
   int t = 0;
-  if constexpr (!PAGED) {
+  if (!PAGED || a.max_pages * pg_size >= kSpreadKeys) {
     const int nfull = max((key_hi - key_begin + 1) / kBN - 2, 0) & ~1;
     for (; t < nfull; t += 2) {
       step(sa, sb, t, std::integral_constant<int, 0>{});

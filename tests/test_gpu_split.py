@@ -105,6 +105,48 @@ def test_ragged_chunks(batch, longest, hq, hkv, d, new, is_query):
         assert torch.equal(back.view(torch.int16), cache.view(torch.int16))
 
 
+@pytest.mark.parametrize("ps", [64, 128, 192, 448])
+@pytest.mark.parametrize("longest,hq,hkv,d,new,is_query", [
+    (8200, 64, 32, 64, 150, False),   # row tiles, transfers spread over the step
+    (8200, 48, 24, 128, 70, True),    # one and two column tiles
+    (9000, 4, 4, 128, 100, False),    # the same over split key ranges
+    (700, 64, 32, 64, 150, True),     # a short cache: transfers at once
+    (3000, 8, 2, 128, 8, False),      # the split-key kernel
+])
+def test_page_sizes(ps, longest, hq, hkv, d, new, is_query):
+    """Pages of one tile and of several, ragged histories that end at their
+    edges: the dense cache's bits."""
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    rng = np.random.default_rng(ps + longest + d)
+    hist = np.array([longest, 5 * ps - new, 2 * ps - 1, 64 * 3, 0], np.int32)
+    lens = np.array([new, new, max(1, new // 3), 1, new], np.int32)
+    B, mp = len(hist), -(-(longest + new) // ps)
+    hist = np.clip(hist, 0, mp * ps - lens)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(int(rng.integers(1 << 30)))
+    rand = lambda *s: torch.randn(s, generator=gen, device="cuda").bfloat16()
+    Kc, Vc = rand(B, hkv, mp * ps, d), rand(B, hkv, mp * ps, d)
+    tab = torch.from_numpy(rng.permutation(B * mp + 3)[:B * mp].reshape(B, mp).astype(np.int32)).cuda()
+    pools = []
+    for cache in (Kc, Vc):
+        pools.append(rand(B * mp + 3, hkv, ps, d))
+        pools[-1][tab.long().reshape(-1)] = cache.view(B, hkv, mp, ps, d).transpose(1, 2).reshape(
+            B * mp, hkv, ps, d)
+    q, k, v = (rand(int(cu[-1]), n, d) for n in (hq, hkv, hkv))
+    tl, tc = torch.from_numpy(hist).cuda(), torch.from_numpy(cu).cuda()
+    announce("page sizes", ps, longest, hq, hkv, d, new, is_query)
+    o, lse = ops.prefill_cached_segment(q, k, v, Kc, Vc, tl, tc, new, is_query)
+    op, lp = ops.prefill_paged(q, k, v, *pools, tab, tl, tc, new, is_query)
+    torch.cuda.synchronize()
+    assert torch.equal(o.view(torch.int16), op.view(torch.int16)) and torch.equal(lse, lp)
+    assert torch.isfinite(lse).all()
+    for cache, pool in zip((Kc, Vc), pools):
+        back = pool[tab.long().reshape(-1)].view(B, mp, hkv, ps, d).transpose(1, 2).reshape(
+            B, hkv, mp * ps, d)
+        assert torch.equal(back.view(torch.int16), cache.view(torch.int16))
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (40, 1, 64)])  # 4 and 40 columns
 def test_decode_workspaces(hq, hkv, d):
     """The same step with every workspace the call accepts, from the smallest
