@@ -5,8 +5,8 @@
 //
 // Work decomposition. The (row, query head) pairs of a dialogue and a set of
 // query heads that share a KV head are the columns of S^T = K Q^T, row-major
-// (head innermost). A workgroup (NWV = 4 or 8 waves) owns 32 NWV consecutive
-// columns, 32 to a wave, so that the K/V tile staged in LDS serves every head
+// (head innermost). A workgroup of four waves owns 128 consecutive columns, 32
+// to a wave, so that the K/V tile staged in LDS serves every head
 // of the set, and a short segment fills whole waves (40 new rows with 4 heads
 // per KV head are 5 waves, where 32-row blocks per head took 8: 40 dialogues
 // of 2000 cached keys 119 -> 109 us). Each wave
@@ -53,6 +53,17 @@ namespace {
 
 constexpr int kBN = 64;  // keys per tile
 constexpr int kQW = 32;  // query rows per wave
+// Four-wave workgroups, two (three at d = 64) to a CU, so that one's prologue
+// and last steps run beside another's products. Eight-wave workgroups stage
+// each K/V tile for twice the columns, half the transfers per product, but are
+// alone on their CU. Four waves against eight (us): packed, 32/8 heads, 8 x 3000
+// 560, 570; 4 x 9000 2243, 2257; 3 x 12000 2945, 2941; 2 x 16384 3625, 3614; but 4
+// ragged up to 16384 5662, 6101; 6 up to 12000 3501, 3851; 16/4 heads, d 64, 2 x
+// 16384 1095, 1143. Cached, 32/8 heads, new rows: 64 over 40 x 2000 keys 126, 135;
+// 2048 over 4 x 16384 2096, 2086; 1000 over 4000 93, 115. (Eight would win where
+// equal dialogues of 129 to 256 columns leave no second round: 40 over 40 x
+// 2000 111, 103; 40 over 20 x 8000 206, 178.)
+constexpr int NWV = 4;
 // Capacity from which a paged cache's transfers are spread over a step's
 // products like the dense cache's, instead of all starting with it. On long
 // key loops the burst costs four-wave workgroups more than eight-wave ones
@@ -65,9 +76,7 @@ constexpr int kSpreadKeys = 8192;
 
 // Waves per SIMD, which bounds registers: d = 64 fits a third wave (4 x 8000
 // tokens, 16 heads: 420 -> 398 us; not the paged cache, which would spill).
-constexpr int fwd_occupancy(int d, int waves, bool paged) {
-  return d == 64 && waves == 4 && !paged ? 3 : 2;
-}
+constexpr int fwd_occupancy(int d, bool paged) { return d == 64 && !paged ? 3 : 2; }
 
 // K and V tiles of 64 keys, row-major, unpadded rows of D bf16 with the
 // swz<D>() chunk swizzle, double-buffered; filled by direct global->LDS
@@ -267,9 +276,9 @@ __device__ __forceinline__ float step_block(const char *kl, const char *vl,
 // workgroup reads its K/V (verifying 8 drafted tokens per dialogue through
 // the cache ran 11 % faster; with several row tiles per group the same bit
 // cost the L2 sharing between them: the workload-3 prefill ran 22 % slower).
-template <int D, bool CACHE, int NWV, bool PAGED, bool NT, bool SPLIT>
+template <int D, bool CACHE, bool PAGED, bool NT, bool SPLIT>
 __global__ void __launch_bounds__(NWV * 64)
-__attribute__((amdgpu_waves_per_eu(fwd_occupancy(D, NWV, PAGED), fwd_occupancy(D, NWV, PAGED))))
+__attribute__((amdgpu_waves_per_eu(fwd_occupancy(D, PAGED), fwd_occupancy(D, PAGED))))
 fwd_kernel(FwdArgs a, int fold, int tiles, int chunk, SplitArgs sp) {
   constexpr int NDB = D / 32;      // 32-wide d blocks of the output
   constexpr int NKS = D / 16;      // 16-deep k steps of Q K^T
@@ -570,52 +579,33 @@ int gcd_int(int x, int y) {
 // mode, where rows are few; packed, the part of it that fills whole waves (a
 // group of 3 as one set ran 12 ragged dialogues up to 900 tokens, 24/8 heads,
 // in 67 us instead of 60).
-int fold_of(const FwdArgs &a, bool cache, int waves) {
+int fold_of(const FwdArgs &a, bool cache) {
   const int g = a.hq / a.hkv;
-  return cache ? g : gcd_int(g, waves);
+  return cache ? g : gcd_int(g, NWV);
 }
 
-int64_t column_tiles(const FwdArgs &a, int fold, int waves) {
-  const int64_t w = waves * kQW;
+int64_t column_tiles(const FwdArgs &a, int fold) {
+  const int64_t w = NWV * kQW;
   return ((int64_t)a.max_rows * fold + w - 1) / w;
 }
 
-template <int D, bool CACHE, int NWV, bool PAGED>
-hipError_t launch_fwd_w(const FwdArgs &a, hipStream_t stream) {
-  const int fold = fold_of(a, CACHE, NWV);
-  const int tiles = (int)column_tiles(a, fold, NWV);
+template <int D, bool CACHE, bool PAGED>
+hipError_t launch_fwd_p(const FwdArgs &a, hipStream_t stream) {
+  const int fold = fold_of(a, CACHE);
+  const int tiles = (int)column_tiles(a, fold);
   const int64_t groups = (int64_t)a.batch * (a.hq / fold);
   if (groups * tiles == 0) return hipSuccess;
   const dim3 grid((unsigned)xcd_grid(groups, tiles));
   if constexpr (CACHE) {
     if (tiles == 1) {
-      hipLaunchKernelGGL((fwd_kernel<D, true, NWV, PAGED, true, false>), grid, dim3(NWV * 64), 0,
+      hipLaunchKernelGGL((fwd_kernel<D, true, PAGED, true, false>), grid, dim3(NWV * 64), 0,
                          stream, a, fold, tiles, ISM_SCHED_CHUNK, SplitArgs{});
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((fwd_kernel<D, CACHE, NWV, PAGED, false, false>), grid, dim3(NWV * 64), 0,
+  hipLaunchKernelGGL((fwd_kernel<D, CACHE, PAGED, false, false>), grid, dim3(NWV * 64), 0,
                      stream, a, fold, tiles, ISM_SCHED_CHUNK, SplitArgs{});
   return hipGetLastError();
-}
-
-// Four-wave workgroups, two (three at d = 64) to a CU, so that one's prologue
-// and last steps run beside another's products. Eight-wave workgroups stage
-// each K/V tile for twice the columns, half the transfers per product, but
-// are alone on their CU: packed with grouped KV heads they still win on long
-// key loops, where the prologue is small. Measured, 8 waves against 4 (us):
-// packed 32/8 heads 2 x 16384 3733, 3752; 6 ragged dialogues up to 3000 348,
-// 330; 24/8 heads 12 x 900 74, 60; cached, 40 new rows over 40 x 2000 keys,
-// 32/8 heads 124, 117; 12 rows over 40 ragged up to 3000, 64/8 heads 139, 91.
-// (Without grouping eight waves would be 256 rows of one head, whose waves
-// finish at different key tiles. In cache mode a ring of four K/V tiles for
-// eight waves alone on their CU measured 124 on the first of these.)
-template <int D, bool CACHE, bool PAGED>
-hipError_t launch_fwd_p(const FwdArgs &a, hipStream_t stream) {
-  if constexpr (!CACHE) {
-    if (a.hq / a.hkv >= 2 && a.max_rows > 8192) return launch_fwd_w<D, false, 8, false>(a, stream);
-  }
-  return launch_fwd_w<D, CACHE, 4, PAGED>(a, stream);
 }
 
 template <int D, bool CACHE>
@@ -628,11 +618,11 @@ template <int D, bool PAGED>
 hipError_t launch_fwd_split_p(const FwdArgs &a, const SplitArgs &sp, hipStream_t stream) {
   const dim3 grid((unsigned)(((int64_t)sp.max_units * a.hkv + 7) / 8 * 8));
   if (sp.col_groups == 1)
-    hipLaunchKernelGGL((fwd_kernel<D, true, 4, PAGED, true, true>), grid, dim3(256), 0, stream, a,
-                       a.hq / a.hkv, 0, 0, sp);
+    hipLaunchKernelGGL((fwd_kernel<D, true, PAGED, true, true>), grid, dim3(NWV * 64), 0, stream,
+                       a, a.hq / a.hkv, 0, 0, sp);
   else
-    hipLaunchKernelGGL((fwd_kernel<D, true, 4, PAGED, false, true>), grid, dim3(256), 0, stream, a,
-                       a.hq / a.hkv, 0, 0, sp);
+    hipLaunchKernelGGL((fwd_kernel<D, true, PAGED, false, true>), grid, dim3(NWV * 64), 0, stream,
+                       a, a.hq / a.hkv, 0, 0, sp);
   const hipError_t err = hipGetLastError();
   return err == hipSuccess && sp.max_splits > 1 ? launch_split_combine(sp, D, stream) : err;
 }
@@ -640,7 +630,7 @@ hipError_t launch_fwd_split_p(const FwdArgs &a, const SplitArgs &sp, hipStream_t
 }  // namespace
 
 hipError_t launch_fwd_split(const FwdArgs &a, const SplitArgs &sp, int d, hipStream_t stream) {
-  if (sp.colw != 4 * kQW || 1 << sp.tile_shift != kBN) return hipErrorInvalidValue;
+  if (sp.colw != NWV * kQW || 1 << sp.tile_shift != kBN) return hipErrorInvalidValue;
   if (d == 128) return a.block_table ? launch_fwd_split_p<128, true>(a, sp, stream)
                                      : launch_fwd_split_p<128, false>(a, sp, stream);
   if (d == 64) return a.block_table ? launch_fwd_split_p<64, true>(a, sp, stream)
