@@ -795,14 +795,14 @@ int gcd_i(int x, int y) {
 }
 
 // dQ workgroups of four waves, two to a CU, so that one's prologue and last
-// steps run beside the other's products; on dialogues above 4096 tokens,
-// where those are a small part, of eight waves, alone on a CU, with half the
-// transfers per product (which also leaves the power-limited chip more clock
-// for the dK/dV kernel behind it). Training steps with four and eight waves
-// (us; two runs differ by 0.3 %): 6 x 5000 tokens, 32 heads 5125, 5091; 6 x
-// 5000, 32/8 heads 4940, 4920; 4 x 8192, 32/8 heads 8460, 8424; 8 x 4000, 32
-// heads 4512, 4504; but 12 ragged up to 3001, 32/8 heads 2889, 2940 and the dQ
-// kernel of 6 ragged up to 900, d 64 18.1, 24.4.
+// steps run beside the other's products; of eight waves, alone on a CU, with
+// half the transfers per product, on dialogues above 4096 tokens, where those
+// are a small part, if all are about that long (with shorter ones among them
+// the last workgroups run alone). Backward passes with four and eight waves
+// (us): 4 x 8192 tokens, 32/8 heads 6739, 6688; d 64 4071, 3984; 32 heads 6646,
+// 6626; 6 x 5000, 32/8 3883, 3880; but 3 x 8000 and 3 x 6000, 32/8 7815, 7873; 12
+// ragged up to 6000 6863, 7077; one of 9000 among 30 of 300 5630, 5853; the dQ
+// kernel of 6 ragged up to 900, 16/4 heads, d 64 18.1, 24.4.
 template <int D, int NWV>
 hipError_t launch_dq(const BwdArgs &a, hipStream_t stream) {
   const int hpw = gcd_i(a.hq / a.hkv, NWV);
@@ -817,8 +817,9 @@ hipError_t launch_dq(const BwdArgs &a, hipStream_t stream) {
 // dQ first: it also writes the per-row summands the dK/dV kernel reads.
 template <int D>
 hipError_t launch_bwd_t(const BwdArgs &a, hipStream_t stream) {
-  hipError_t err =
-      a.max_seqlen > 4096 ? launch_dq<D, 8>(a, stream) : launch_dq<D, 4>(a, stream);
+  const bool equal = (int64_t)a.total * 10 >= (int64_t)a.batch * a.max_seqlen * 9;
+  hipError_t err = a.max_seqlen > 4096 && equal ? launch_dq<D, 8>(a, stream)
+                                                : launch_dq<D, 4>(a, stream);
   if (err != hipSuccess) return err;
   const int ktiles = (a.max_seqlen + kKW - 1) / kKW, parts = a.dkv_part ? a.dkv_parts : 1;
   hipLaunchKernelGGL((dkv_kernel<D>),
