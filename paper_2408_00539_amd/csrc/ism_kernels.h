@@ -121,12 +121,12 @@ hipError_t launch_decode(const DecodeArgs &a, int d, hipStream_t stream);
 // Which kernel a decode step takes, with G = hq / hkv query heads per KV head:
 // the vector kernel (ism_decode.hip) when the step has kDecodeVectorSlabs or
 // more (dialogue, KV head) slabs and no divisor of G lies in 4 .. 32, else the
-// split-key matrix-core kernel (ism_split.hip). Below that slab count the
-// latter's long one-wave chunks stream faster even for one query head (256
-// slabs of 8192 positions: 6.5 TB/s against 6.2, 6.0 and 5.9 for 1, 2 and 3
-// heads; 64 slabs: 5.6 against 5.2, 4.8 and 4.2); from 1024 slabs on the
-// vector kernel's wider grid is faster for 1-3 heads (6.9, 6.7, 6.7 against
-// 6.4).
+// split-key matrix-core kernel (ism_split.hip). Vector against split-key (us),
+// d 128, 1 and 3 query heads per KV head: 256 slabs of 8192 keys 173, 162 and
+// 180, 162; 320 of 3000 80, 77 and 85, 77; 384 of 8192 240, 241 and 255, 242;
+// 512 of 8192 322, 315 and 338, 315; 512 of 3000 120, 122 and 128, 123; 576 of
+// 8192 363, 394 and 384, 394; 1024 of 3000 234, 246 and 246, 247 (ragged, one
+// head 139, 157); 1600 of 3000 364, 392 and 388, 394.
 constexpr int kDecodeVectorSlabs = 512;
 // The head set whose partials size the smallest workspace a step accepts (the
 // largest divisor of G up to 32; 0: a vector-kernel step).
