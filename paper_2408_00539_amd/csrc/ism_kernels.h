@@ -169,7 +169,7 @@ struct SplitArgs {
   int32_t colw;              // columns (row, head) per workgroup: 32, or 128 (row-tiled)
   int32_t col_groups;        // column groups of the longest dialogue
   int32_t col_stride;        // columns per partials slot
-  int32_t budget;            // units (chunk, column group) per KV head at most (0: any fit)
+  int32_t budget;            // units (chunk, column group) per KV head to fill (0: any fit)
   int32_t max_units;         // bound of the units per KV head
   int32_t max_splits;        // chunks per dialogue at most
   int32_t tile_shift;        // log2 of the keys per tile (32 or 64)

@@ -135,14 +135,14 @@ __device__ __forceinline__ int units_of(const SplitArgs &a, const Entry &x, int 
 }
 
 // Tiles per chunk at most: a length for which the chunks of all dialogues,
-// sum n_b groups_b, are at most `budget`, which bounds the grid on the host
-// (budget >= sum groups_b, so that one chunk per dialogue always fits; the
-// same sums in every workgroup). A one-wave launch with its dialogues in
-// registers counts the chunks of each length tried: first the one that fills
-// the budget if every dialogue's last chunk is half full (equal dialogues then
-// get as many chunks as the budget holds), then lengths that make room for
-// what rounding up did add. Others take the length whose bound, sum t_b
-// groups_b / lc + sum groups_b, fits.
+// sum n_b groups_b, are at most the grid's units per KV head, which the host
+// bounds: `budget`, or budget + sum groups_b for the row-tiled kernel (one
+// chunk per dialogue always fits; the same sums in every workgroup). A
+// one-wave launch with its dialogues in registers counts the chunks of each
+// length tried: first the one that fills the budget if every dialogue's last
+// chunk is half full (equal dialogues then get as many chunks as the budget
+// holds), then lengths that make room for what rounding up did add. Others
+// take the length whose bound, sum t_b groups_b / lc + sum groups_b, fits.
 __device__ __forceinline__ int chunk_limit(const SplitArgs &a, int lane, const Entry (&w)[kWaves]) {
   constexpr int kLongest = 1 << 26;  // tiles: any dialogue is one chunk
   float sum = (float)w[0].t * (float)w[0].g, groups = (float)w[0].g;
@@ -161,7 +161,7 @@ __device__ __forceinline__ int chunk_limit(const SplitArgs &a, int lane, const E
   groups = wave_total(groups);
   const float budget = (float)a.budget;
   const bool count = a.colw == 32 && a.batch <= 64 * kWaves;
-  float units = budget - (count ? 0.5f : 1.f) * groups;
+  float units = a.colw != 32 ? budget : budget - (count ? 0.5f : 1.f) * groups;
   for (int lc = 0;;) {
     // sum / units, rounded up
     const float l = units >= 1.f ? sum * __builtin_amdgcn_rcpf(units) * 1.0001f : 1e9f;

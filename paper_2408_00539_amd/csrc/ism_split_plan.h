@@ -104,10 +104,11 @@ inline SplitPlan split_plan(SplitKind kind, int32_t batch, int64_t total_rows, i
   const int64_t whole = all_groups * hkv;  // units if no dialogue is cut
   int64_t target = p.col_stride > 16 && whole <= 512 ? kSplitUnits32 : kSplitUnits;
   if (whole >= target) target = whole + whole / 8 + 256;
-  if (!one_wave) target = whole + kSplitUnits128;
-  p.budget = (int32_t)(target / hkv);
+  // (row-tiled: the units aimed at, to which rounding up adds one per group)
+  p.budget = (int32_t)(one_wave ? target / hkv : (kSplitUnits128 + hkv - 1) / hkv);
+  const int64_t bound = one_wave ? p.budget : p.budget + all_groups;
   int64_t units = all_groups * p.max_splits;
-  if (fixed <= 0 && units > p.budget) units = p.budget;
+  if (fixed <= 0 && units > bound) units = bound;
   else if (one_wave) p.budget = 0;
   auto layout = [&](int64_t n) {
     p.max_units = (int32_t)n;

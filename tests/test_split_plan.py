@@ -83,7 +83,7 @@ def units(p, cached, rows, group, cap, fixed=0):
         total, longest = np.float32((t * g).sum()), 1 << 26
 
         groups, lc, count = int(g.sum()), 0, p.colw == 32 and len(rows) <= 256
-        room = p.budget - groups * (0.5 if count else 1)
+        room = p.budget - groups * (0 if p.colw != 32 else 0.5 if count else 1)
         while True:
             x = np.float32(total / np.float32(max(room, 1)) * np.float32(1.0001))
             lc = max(int(min(x if room >= 1 else 1e9, longest)) + 1, p.min_tiles,
