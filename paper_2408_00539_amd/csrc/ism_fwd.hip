@@ -575,13 +575,23 @@ int gcd_int(int x, int y) {
   return x;
 }
 
-// Query heads folded into a workgroup's columns: the whole group in cache
-// mode, where rows are few; packed, the part of it that fills whole waves (a
-// group of 3 as one set ran 12 ragged dialogues up to 900 tokens, 24/8 heads,
-// in 67 us instead of 60).
+// Query heads folded into a workgroup's columns. Packed: the part of the group
+// that fills whole waves (a group of 3 as one set ran 12 ragged dialogues up to
+// 900 tokens, 24/8 heads, in 67 us instead of 60). In cache mode, where rows are
+// few, the whole group; but a group's workgroups share an XCD, so when fewer
+// than 32 groups would load the 8 XCDs unevenly, sets of 8 heads and more that
+// still fill workgroups. Whole group, sets of 8 (us): 200 rows over 8 ragged
+// dialogues up to 3000 keys, 32/2 heads 80, 66 (four other layouts 77-85,
+// 65-71); 800 rows over 4 ragged up to 8000, 64/2 810, 603; 300 over 8 x 3000,
+// 64/2 247, 248; but 14 over 40 x 2000, 32/2 40, 49 and 30 x 3000, 64/4 56, 78.
 int fold_of(const FwdArgs &a, bool cache) {
   const int g = a.hq / a.hkv;
-  return cache ? g : gcd_int(g, NWV);
+  if (!cache) return gcd_int(g, NWV);
+  int fold = g;
+  while (fold >= 16 && fold % 2 == 0 && (int64_t)a.batch * (a.hq / fold) < 32 &&
+         (int64_t)a.max_rows * (fold / 2) >= NWV * kQW)
+    fold /= 2;
+  return fold;
 }
 
 int64_t column_tiles(const FwdArgs &a, int fold) {

@@ -50,6 +50,9 @@ def _hist(rng, batch, longest):
     (3, 5000, 3, 1, 128, 33, False),
     (8, 9000, 4, 4, 64, 100, False),
     (11, 1100, 16, 1, 64, 40, True),
+    # the row-tiled kernel with a group's heads in two and four sets
+    (4, 700, 32, 2, 64, 230, False),
+    (2, 300, 192, 3, 64, 300, True),
     # one new row whose heads alone fill more than one 32-column block
     (5, 4000, 40, 1, 64, 1, True),
     (4, 8000, 64, 1, 128, 1, False),
