@@ -1,9 +1,10 @@
 """GPU parity of the split-key cache kernels (ism_split.hip, and the forward
-kernel over the same plan) where the plan and the tiles can go wrong: column counts (new rows x query heads per KV head)
-around one 32-column block, histories at the edges of the 32-key tiles, more
-dialogues than lanes of the planning wave, dialogues without new rows, ragged
-lengths that are cut into one to many chunks, workspaces from none to full,
-and out-of-contract lengths. Against the fp64 oracle, with outputs filled
+kernel over the same plan) where the plan and the tiles can go wrong: column
+counts (new rows x query heads per KV head) around one 32-column block,
+histories at the edges of the 32-key tiles, more dialogues than lanes of the
+planning wave, dialogues without new rows, ragged lengths that are cut into one
+to many chunks, decode workspaces from the smallest to more than is used,
+prefill workspaces from none to full, and out-of-contract lengths. Against the fp64 oracle, with outputs filled
 with NaN; paged equal to dense bit for bit, and the caches after the append
 equal to the inputs.
 """
@@ -150,35 +151,55 @@ def test_page_sizes(ps, longest, hq, hkv, d, new, is_query):
         assert torch.equal(back.view(torch.int16), cache.view(torch.int16))
 
 
-@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 128), (40, 1, 64)])  # 4 and 40 columns
-def test_decode_workspaces(hq, hkv, d):
-    """The same step with every workspace the call accepts, from the smallest
-    (fewer chunks, down to one per dialogue) to more than it uses; one
-    dialogue's position lies outside the cache (NaN, nothing appended)."""
+def _least_decode_workspace(B, max_len, hq, hkv, d, splits):
+    """The smallest workspace a matrix-core decode step accepts: the partials
+    of one chunk per 256 keys, at most 64 and at most 768 head sets, or of the
+    asked-for chunks."""
+    g = hq // hkv
+    sets = hq // max(x for x in range(1, min(g, 32) + 1) if g % x == 0)
+    s = splits or max(1, min(-(-768 // (B * sets)), -(-max_len // 256), 64))
+    up = lambda n: -(-n // 256) * 256
+    return up(B * hq * s * d * 4) + up(B * hq * s * 8)
+
+
+@pytest.mark.parametrize("hq,hkv,d,cap,splits", [
+    (8, 2, 128, 3000, 0),    # 4 columns
+    (40, 1, 64, 3000, 0),    # 40: two column groups
+    (33, 1, 64, 256, 0),     # the smallest holds one chunk per dialogue
+    (8, 2, 128, 3000, 7),    # asked-for chunks, and fewer in a smaller one
+    (33, 1, 64, 900, 3),     # one of three
+])
+def test_decode_workspaces(hq, hkv, d, cap, splits):
+    """The same step in workspaces from the smallest that is accepted (fewer
+    chunks, down to one per dialogue) to more than it uses, and 256 bytes less
+    than the smallest (refused); one dialogue's position lies outside the cache
+    (NaN, nothing appended)."""
     torch = torch_cuda()
     from paper_2408_00539_amd import ops
-    rng = np.random.default_rng(hq + d)
-    B, cap = 9, 3000
-    pos = np.array([0, 1, 31, 32, 2999, 3000, 1500, 700, 64], np.int32)
+    rng = np.random.default_rng(hq + d + cap + splits)
+    pos = np.array([0, 1, 31, 32, cap - 1, cap, cap // 2, cap // 4, 64], np.int32)
+    B = len(pos)
     kc, vc = _bits(rng, B, hkv, cap, d), _bits(rng, B, hkv, cap, d)
     q, k, v = _bits(rng, B, hq, d), _bits(rng, B, hkv, d), _bits(rng, B, hkv, d)
     want = [oracle.decode_step(f64(kc[b, :, :p]).transpose(1, 0, 2),
                                f64(vc[b, :, :p]).transpose(1, 0, 2), f64(q[b]), f64(k[b]),
                                f64(v[b]), 1 / np.sqrt(d))[:2] if p < cap else None
             for b, p in enumerate(pos)]
-    full = ops.workspace_size(ops.ISM_OP_DECODE, B, 0, cap, hq, hkv, d)
-    least = full
-    for nbytes in (full + 4096, full, full // 2 // 256 * 256, full // 8 // 256 * 256, 256):
+    full = ops.workspace_size(ops.ISM_OP_DECODE, B, 0, cap, hq, hkv, d, splits)
+    least = _least_decode_workspace(B, cap, hq, hkv, d, splits)
+    assert least < full
+
+    def step(nbytes):
         Kc, Vc = dev_bf16(kc), dev_bf16(vc)
         ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-        announce("decode workspace", hq, hkv, d, nbytes)
-        try:
-            o, lse = ops.decode(dev_bf16(q), dev_bf16(k), dev_bf16(v), Kc, Vc,
-                                torch.from_numpy(pos).cuda(), workspace=ws)
-        except ops.IsmError as e:
-            assert "ISM_ERR_WORKSPACE" in str(e) and nbytes < full
-            continue
-        least = min(least, nbytes)
+        announce("decode workspace", hq, hkv, d, cap, splits, nbytes)
+        return (Kc, *ops.decode(dev_bf16(q), dev_bf16(k), dev_bf16(v), Kc, Vc,
+                                torch.from_numpy(pos).cuda(), workspace=ws, num_splits=splits))
+
+    with pytest.raises(ops.IsmError, match="ISM_ERR_WORKSPACE"):
+        step(least - 256)
+    for nbytes in (least, least + 4096, (least + full) // 512 * 256, full - 256, full, full + 4096):
+        Kc, o, lse = step(nbytes)
         o, lse = host_f64(o), host_f64(lse)
         got = Kc.view(torch.int16).cpu().numpy().view(np.uint16)
         for b, p in enumerate(pos):
@@ -189,4 +210,74 @@ def test_decode_workspaces(hq, hkv, d):
             compare(f"O ws {nbytes} b{b}", o[b], want[b][0])
             compare(f"LSE ws {nbytes} b{b}", lse[:, b], want[b][1])
             np.testing.assert_array_equal(got[b, :, p], k[b])
-    assert least < full or hkv == 1
+
+
+@pytest.mark.parametrize("longest,hq,hkv,d,new,is_query", [
+    (2100, 8, 2, 128, 8, False),      # 32 columns: split, or row-tiled with an append launch
+    (2100, 4, 1, 128, 150, True),     # row-tiled: split, or not
+    (4000, 64, 1, 64, 1, False),
+])
+def test_prefill_workspaces(longest, hq, hkv, d, new, is_query):
+    """A prefill that would split its keys, given no workspace, one that is too
+    small or misaligned, and its own: the oracle's result and the same caches in
+    each, paged equal to dense bit for bit."""
+    torch = torch_cuda()
+    from paper_2408_00539_amd import ops
+    rng = np.random.default_rng(longest + hq + new)
+    B, ps = 5, 64
+    hist = np.array([longest, longest // 2, 129, 64, 0], np.int32)
+    lens = np.array([new, max(1, new // 2), 1, new, new], np.int32)
+    cap = -(-(longest + new) // ps) * ps
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    Tn, mp = int(cu[-1]), cap // ps
+    kc, vc = _bits(rng, B, hkv, cap, d), _bits(rng, B, hkv, cap, d)
+    q, k, v = (_bits(rng, Tn, n, d) for n in (hq, hkv, hkv))
+    need = ops.prefill_workspace_size(B, Tn, new, hq, hkv, d, cap)
+    assert need > 0
+    ro, rl = np.empty((Tn, hq, d)), np.empty((hq, Tn))
+    want_k = kc.copy()
+    for b in range(B):
+        r, C, L = slice(cu[b], cu[b + 1]), int(hist[b]), int(lens[b])
+        ro[r], rl[:, r], _, _ = oracle.prefill_cached(
+            f64(kc[b, :, :C]).transpose(1, 0, 2), f64(vc[b, :, :C]).transpose(1, 0, 2), f64(q[r]),
+            f64(k[r]), f64(v[r]), 1 / np.sqrt(d), new_is_query=is_query)
+        want_k[b, :, C:C + L] = k[r].transpose(1, 0, 2)
+    dev = dev_bf16(q), dev_bf16(k), dev_bf16(v)
+    tl, tc = torch.from_numpy(hist).cuda(), torch.from_numpy(cu).cuda()
+    tab = torch.from_numpy(rng.permutation(B * mp).reshape(B, mp).astype(np.int32)).cuda()
+    ws = torch.empty(need + 512, dtype=torch.uint8, device="cuda")
+    ptr = lambda t: t.data_ptr()
+    stream, scale = torch.cuda.current_stream().cuda_stream, 1 / np.sqrt(d)
+    for off, nbytes in ((None, 0), (0, need - 256), (128, need), (0, need)):
+        got = []
+        for paged in (False, True):
+            Kc, Vc = dev_bf16(kc), dev_bf16(vc)
+            if paged:
+                pools = []
+                for cache in (Kc, Vc):
+                    pools.append(torch.zeros((B * mp, hkv, ps, d), dtype=cache.dtype, device="cuda"))
+                    pools[-1][tab.long().reshape(-1)] = cache.view(B, hkv, mp, ps, d).transpose(
+                        1, 2).reshape(B * mp, hkv, ps, d)
+            o = torch.full((Tn, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+            lse = torch.full((hq, Tn), float("nan"), device="cuda")
+            tail = (ptr(o), ptr(lse), hq, hkv, d, scale, None if off is None else ptr(ws) + off,
+                    nbytes, stream)
+            announce("prefill workspace", longest, hq, hkv, d, new, is_query, off, nbytes, paged)
+            head = (ptr(tc), B, Tn, new, int(is_query), *map(ptr, dev))
+            if paged:
+                st = ops.lib().ism_attn_prefill_paged(*head, *map(ptr, pools), B * mp, ps, ptr(tab),
+                                                      mp, ptr(tl), *tail)
+            else:
+                st = ops.lib().ism_attn_prefill_cached_segment(*head, ptr(Kc), ptr(Vc), cap, ptr(tl),
+                                                               *tail)
+            assert st == 0
+            torch.cuda.synchronize()
+            if paged:
+                Kc = pools[0][tab.long().reshape(-1)].view(B, mp, hkv, ps, d).transpose(
+                    1, 2).reshape(B, hkv, cap, d)
+            np.testing.assert_array_equal(Kc.view(torch.int16).cpu().numpy().view(np.uint16), want_k)
+            got.append((o, lse))
+        assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16))
+        assert torch.equal(got[0][1], got[1][1])
+        compare(f"O ws {off} {nbytes}", host_f64(got[0][0]), ro)
+        compare(f"LSE ws {off} {nbytes}", host_f64(got[0][1]), rl)
