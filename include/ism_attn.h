@@ -95,8 +95,9 @@ size_t ism_attn_workspace_size(int32_t op, int32_t batch, int32_t total_tokens,
 /* Bytes of the optional workspace of a cached prefill (dense, paged or with
  * 2-D positions; cache_cap = max_pages * page_size for a paged cache). A
  * prefill that is given at least this much (256-byte aligned) may split its
- * dialogues' key ranges over workgroups; without a workspace it runs
- * unsplit, with the same result to rounding. 0: a workspace is not used. */
+ * dialogues' key ranges over workgroups (at places that depend on the whole
+ * batch's lengths); without a workspace it runs unsplit, with the same
+ * result to rounding. 0: a workspace is not used. */
 size_t ism_attn_prefill_workspace_size(int32_t batch, int32_t total_new,
                                        int32_t max_new, int32_t hq,
                                        int32_t hkv, int32_t d,
