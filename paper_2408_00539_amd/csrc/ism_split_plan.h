@@ -61,10 +61,12 @@ struct SplitPlan {
 // 107, 103, 119; 64 x 4000 169, 165, 175; 100 x 8192 (800 units whole) 611,
 // 561, 606. Partials of 17 columns and more weigh more (8 rows, 32/8 heads, 8 x
 // 3000 29.5, 31.9, 32.1; decode, 32/1 heads, 16 x 8192 26.5, 29.3, -), so those
-// take 768 while dialogues need cutting. A call that fills the chip with whole
+// take 768 while dialogues need cutting, and so do calls of few slabs, whose
+// chunks are short (12 x 4000, 16/4 heads 22.9, 24.1; 20 ragged up to 5000, d 64
+// 24.4, 25.8; but 24 ragged up to 6000, 32/8 67.1, 65.1). A call that fills the chip with whole
 // dialogues has an eighth of them and 256 more for the long ones. Row-tiled
 // launches, whose partials weigh most, cut for 448 units (two to a CU).
-constexpr int kSplitUnits = 1024, kSplitUnits32 = 768, kSplitUnits128 = 448;
+constexpr int kSplitUnits = 1024, kSplitUnitsFew = 768, kSplitUnits128 = 448;
 // From this many (dialogue, KV head, column group) workgroups on, a one-wave
 // launch keeps every dialogue whole and needs no plan, whose scans over many
 // dialogues every workgroup would repeat. Measured with the plan and without
@@ -102,7 +104,8 @@ inline SplitPlan split_plan(SplitKind kind, int32_t batch, int64_t total_rows, i
   const int64_t all_groups = by_rows < (int64_t)batch * groups ? by_rows : (int64_t)batch * groups;
   const int64_t per = (int64_t)hkv * p.col_stride * (d + 2) * 4;
   const int64_t whole = all_groups * hkv;  // units if no dialogue is cut
-  int64_t target = p.col_stride > 16 && whole <= 512 ? kSplitUnits32 : kSplitUnits;
+  const bool few = whole <= 160 || (p.col_stride > 16 && whole <= 512);
+  int64_t target = few ? kSplitUnitsFew : kSplitUnits;
   if (whole >= target) target = whole + whole / 8 + 256;
   // (row-tiled: the units aimed at, to which rounding up adds one per group)
   p.budget = (int32_t)(one_wave ? target / hkv : (kSplitUnits128 + hkv - 1) / hkv);
