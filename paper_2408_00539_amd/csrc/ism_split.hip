@@ -275,6 +275,11 @@ split_combine_kernel(SplitArgs a) {
   const Extent x = extent_from(a, r.r0, r.rows, r.cached);
   const int ncol = x.rows * a.hq, n = pl[0], groups = groups_of(a, x.rows);
   if (ncol == 0 || n <= 1) return;
+  // (out-of-contract row ranges can ask for more units than the host made room
+  // for: the dialogues past it left no entry, and nothing is read for them)
+  if (n > a.max_splits ||
+      (uint32_t)pl[1] + (int64_t)n * a.hkv * groups > (int64_t)a.max_units * a.hkv)
+    return;
   const int64_t step = (int64_t)a.hkv * groups * a.col_stride;  // between chunks
   for (int col = (int)blockIdx.x * 4 + wave; col < ncol; col += (int)gridDim.x * 4) {
     const int row = col / a.hq, head = col - row * a.hq, kvh = head / a.group;
